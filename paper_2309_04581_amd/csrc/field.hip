@@ -9,6 +9,7 @@
 
 #include "mr_device.h"
 #include "mr_field_kernels.h"
+#include "mr_mfma.h"
 
 using namespace mr;
 
@@ -26,52 +27,140 @@ uint16_t bf16_rne(float f) {
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
-// occupancy: one thread per cell, 8 density probes at the sub-cell centres
+// Occupancy grid.  A cell is occupied when sigma >= thresh at any of its 8
+// sub-cell centres.  The density MLP runs on the matrix cores, a wave taking
+// 64 consecutive cells as 8 runs of 8 cells x 4 tiles: the columns of tile t
+// are the two x sub-cells of the run's 8 cells at the (y, z) sub-cell t.
+//
+// The grid is defined by the per-thread FP32 evaluation below (probe_sigma,
+// whose products and sums come in another order), so the tiles only decide
+// the cells they decide for certain: the two evaluations of a raw density
+// differ by at most the rounding of their sums, bounded by kOccBand times
+// max|f| sum_j |W1_j| sum_i |W0_ji| (each has about a hundred roundings of
+// 2^-24 in sequence; 2e-5 covers both three times over).  A cell whose 8
+// probes are neither one of them surely >= thresh nor all surely below it is
+// evaluated per thread.  With the vector-unit MLP on every probe the 128^3
+// grid of a 16-level field took 8.95 ms.
+constexpr float kOccBand = 2e-5f;
+
+// sigma of one probe on one thread: every hidden sum runs over the features in
+// order and the output over the hidden units in order.  The sums are kept
+// level by level (64 registers), the weights read as scalars through the
+// constant address space.
 template <int NL, typename TabT>
-__global__ __launch_bounds__(256) void k_occupancy(FieldView F, const TabT* __restrict__ table, int res,
-                                                   float thresh, uint32_t* __restrict__ words,
-                                                   uint8_t* __restrict__ bytes) {
-  __shared__ __align__(16) float sW[2048 + 1024];
-  for (int i = threadIdx.x; i < 2048 + 1024; i += blockDim.x) sW[i] = F.mlp[i];
-  __syncthreads();
-  const int64_t n = (int64_t)res * res * res;
-  const int64_t nwave_cells = ((n + 63) / 64) * 64;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nwave_cells;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    bool occ = false;
-    if (c < n) {
-      const int cx = (int)(c % res), cy = (int)((c / res) % res), cz = (int)(c / ((int64_t)res * res));
-      float best = -INFINITY;
-      for (int s = 0; s < 8; ++s) {
-        const float xh = (cx + 0.25f + 0.5f * (s & 1)) / res;
-        const float yh = (cy + 0.25f + 0.5f * ((s >> 1) & 1)) / res;
-        const float zh = (cz + 0.25f + 0.5f * ((s >> 2) & 1)) / res;
-        const float px = F.amin[0] + xh * (F.amax[0] - F.amin[0]);
-        const float py = F.amin[1] + yh * (F.amax[1] - F.amin[1]);
-        const float pz = F.amin[2] + zh * (F.amax[2] - F.amin[2]);
-        float feat[32], raw[16];
-        hash_encode<NL, TabT>(F, table, px, py, pz, feat);
-        density_mlp<NL>(sW, feat, raw);
-        best = fmaxf(best, softplusf(raw[0] + F.density_offset));
-      }
-      occ = best >= thresh;
-      if (bytes) bytes[c] = occ ? 1 : 0;
+__device__ __forceinline__ float probe_sigma(const FieldView& F, const TabT* __restrict__ table, float px, float py,
+                                             float pz) {
+  typedef const __attribute__((address_space(4))) float* ConstF;
+  const ConstF W0 = (ConstF)F.mlp;            // [64][32]
+  const ConstF W1 = (ConstF)(F.mlp + 2048);   // row 0 of [16][64]
+  float xh, yh, zh, h[64];
+  to_unit(F, px, py, pz, xh, yh, zh);
+#pragma unroll
+  for (int j = 0; j < 64; ++j) h[j] = 0.0f;
+#pragma unroll 1
+  for (int l = 0; l < NL; ++l) {
+    float f0, f1;
+    encode_level<TabT>(F, table, xh, yh, zh, l, f0, f1);
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+      h[j] += W0[j * 32 + 2 * l] * f0;
+      h[j] += W0[j * 32 + 2 * l + 1] * f1;
     }
-    // a wave covers 64 consecutive cells = two whole words
-    const uint64_t m = __ballot(occ);
-    const int lane = threadIdx.x & 63;
-    const int64_t w0 = (c - lane) >> 5;
-    if (lane == 0 && w0 * 32 < n) words[w0] = (uint32_t)m;
-    if (lane == 1 && (w0 + 1) * 32 < n) words[w0 + 1] = (uint32_t)(m >> 32);
+  }
+  float r = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 64; ++j) r += W1[j] * fmaxf(h[j], 0.0f);
+  return softplusf(r + F.density_offset);
+}
+
+__device__ __forceinline__ void probe_point(const FieldView& F, int res, int64_t c, int s, float& px, float& py,
+                                            float& pz) {
+  const int cx = (int)(c % res), cy = (int)((c / res) % res), cz = (int)(c / ((int64_t)res * res));
+  const float xh = (cx + 0.25f + 0.5f * (s & 1)) / res;
+  const float yh = (cy + 0.25f + 0.5f * ((s >> 1) & 1)) / res;
+  const float zh = (cz + 0.25f + 0.5f * ((s >> 2) & 1)) / res;
+  px = F.amin[0] + xh * (F.amax[0] - F.amin[0]);
+  py = F.amin[1] + yh * (F.amax[1] - F.amin[1]);
+  pz = F.amin[2] + zh * (F.amax[2] - F.amin[2]);
+}
+
+template <int NL, typename TabT>
+__global__ __launch_bounds__(256) void k_occupancy(FieldView F, const TabT* __restrict__ table,
+                                                   const uint32_t* __restrict__ frags, int res, float thresh,
+                                                   uint32_t* __restrict__ words, uint8_t* __restrict__ bytes) {
+  using LY = FragLayout<NL, 4, 1, false>;   // the density layers come first and are the same for every layout
+  __shared__ __align__(16) uint32_t sW[LY::C1];
+  __shared__ float s_norm;
+  for (int i = threadIdx.x; i < LY::C1; i += blockDim.x) sW[i] = frags[i];
+  const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
+  if (threadIdx.x < 64) {   // sum_j |W1_j| sum_i |W0_ji| over the 64 hidden units
+    float a = 0.0f;
+    for (int i = 0; i < 2 * NL; ++i) a += fabsf(F.mlp[lane * 32 + i]);
+    a *= fabsf(F.mlp[2048 + lane]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+    if (lane == 0) s_norm = a;
+  }
+  __syncthreads();
+  const float norm = s_norm;
+  const int64_t n = (int64_t)res * res * res;
+  const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
+  for (int64_t w = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); w * 64 < n; w += waves) {
+    uint64_t occ = 0, open = 0;   // bit i: cell 64 w + i surely occupied / undecided
+#pragma unroll 1
+    for (int run = 0; run < 8; ++run) {
+      const int64_t c = min(w * 64 + run * 8 + (j >> 1), n - 1);
+      bool yes = false, maybe = false;
+#pragma unroll 1
+      for (int t = 0; t < 4; ++t) {
+        float px, py, pz;
+        probe_point(F, res, c, 2 * t + (j & 1), px, py, pz);
+        float fe[LY::NF];
+        encode_group<NL, TabT>(F, table, px, py, pz, g, fe);
+        float fm = 0.0f;
+#pragma unroll
+        for (int k = 0; k < LY::NF; ++k) fm = fmaxf(fm, fabsf(fe[k]));
+        fm = fmaxf(fm, __shfl_xor(fm, 16, 64));
+        fm = fmaxf(fm, __shfl_xor(fm, 32, 64));
+        const f4v raw = density_raw<NL, 4, 1, false>(sW, fe, lane);
+        const float band = kOccBand * fm * norm + 1e-6f * fabsf(F.density_offset);
+        const float r = raw[0] + F.density_offset;   // lanes 0..15: raw output 0 of sample j
+        yes |= softplusf(r - band) * 0.9999f >= thresh;
+        maybe |= !(softplusf(r + band) * 1.0001f < thresh);
+      }
+      const uint64_t my = __ballot(yes), mm = __ballot(maybe);
+      // columns 2i, 2i + 1 are cell i of the run
+      uint32_t a = ((uint32_t)my | ((uint32_t)my >> 1)) & 0x5555u, b = ((uint32_t)mm | ((uint32_t)mm >> 1)) & 0x5555u;
+      a = (a | (a >> 1)) & 0x3333u; a = (a | (a >> 2)) & 0x0F0Fu; a = (a | (a >> 4)) & 0xFFu;
+      b = (b | (b >> 1)) & 0x3333u; b = (b | (b >> 2)) & 0x0F0Fu; b = (b | (b >> 4)) & 0xFFu;
+      occ |= (uint64_t)a << (8 * run);
+      open |= (uint64_t)(b & ~a) << (8 * run);
+    }
+    const int64_t c = w * 64 + lane;
+    bool o = c < n && ((occ >> lane) & 1u);
+    if (c < n && ((open >> lane) & 1u)) {
+      float best = -INFINITY;
+#pragma unroll 1
+      for (int s = 0; s < 8; ++s) {
+        float px, py, pz;
+        probe_point(F, res, c, s, px, py, pz);
+        best = fmaxf(best, probe_sigma<NL, TabT>(F, table, px, py, pz));
+      }
+      o = best >= thresh;
+    }
+    if (bytes && c < n) bytes[c] = o ? 1 : 0;
+    const uint64_t m = __ballot(o);
+    if (lane == 0) words[2 * w] = (uint32_t)m;
+    if (lane == 1 && (2 * w + 1) * 32 < n) words[2 * w + 1] = (uint32_t)(m >> 32);
   }
 }
 
 template <int NL, typename TabT>
 mr_status launch_occ(mr_field* f, int res, float thresh, uint8_t* bytes, hipStream_t st) {
   const int64_t n = (int64_t)res * res * res;
-  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 16384);
+  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 2048);
   hipLaunchKernelGGL((k_occupancy<NL, TabT>), dim3(blocks), dim3(256), 0, st, f->view,
-                     reinterpret_cast<const TabT*>(f->table_dev), res, thresh, f->occ_dev, bytes);
+                     reinterpret_cast<const TabT*>(f->table_dev), f->frag_f32_dev, res, thresh, f->occ_dev, bytes);
   MR_HIP(hipGetLastError());
   return MR_OK;
 }

@@ -1,6 +1,5 @@
 // Device building blocks of the marcher: Philox, hash-grid encoding, SH, the
-// per-thread density MLP of the occupancy grid, the watertight ray-triangle
-// test and BVH traversal with a per-thread stack in LDS.
+// watertight ray-triangle test and BVH traversal with a per-thread stack in LDS.
 #pragma once
 #include "mr_common.h"
 
@@ -185,37 +184,6 @@ __device__ __forceinline__ float softplusf(float x) {
   const float w = 1.0f + v;
   const float l = w == 1.0f ? v : 0.6931471805599453f * __builtin_amdgcn_logf(w) * (v / (w - 1.0f));
   return fmaxf(x, 0.0f) + l;
-}
-
-// ---------------------------------------------------------------------------
-// density MLP on one sample per lane (occupancy grid), weights broadcast from
-// LDS: W0 [64][32] at 0, W1 [16][64] at 2048.
-// ---------------------------------------------------------------------------
-
-template <int NIN>
-__device__ __forceinline__ float dot_row(const float* __restrict__ w, const float* x) {
-  float acc = 0.0f;
-#pragma unroll
-  for (int i = 0; i < NIN; i += 4) {
-    const float4 q = *reinterpret_cast<const float4*>(w + i);
-    acc += q.x * x[i];
-    if (i + 1 < NIN) acc += q.y * x[i + 1];
-    if (i + 2 < NIN) acc += q.z * x[i + 2];
-    if (i + 3 < NIN) acc += q.w * x[i + 3];
-  }
-  return acc;
-}
-
-// density MLP: 2*NL features -> 64 (ReLU) -> 16 raw outputs
-template <int NL>
-__device__ __forceinline__ void density_mlp(const float* __restrict__ W, const float* feat, float* raw) {
-#pragma unroll
-  for (int k = 0; k < 16; ++k) raw[k] = 0.0f;
-  for (int j = 0; j < 64; ++j) {
-    const float h = fmaxf(dot_row<2 * NL>(W + 0 + j * 32, feat), 0.0f);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) raw[k] += W[2048 + k * 64 + j] * h;
-  }
 }
 
 // ---------------------------------------------------------------------------

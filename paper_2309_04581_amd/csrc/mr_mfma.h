@@ -204,16 +204,12 @@ __device__ __forceinline__ void encode_level(const FieldView& F, const TabT* __r
   }
 }
 
-// The MLPs on a 16-sample tile.  fe: this lane's features (its level group,
-// its sample); u[mt][v]: the colour layer-1 contribution of the SH inputs for
-// hidden row mt*16 + 4g + v (per lane's sample); W: fragments in LDS.
-// Returns sigma and rgb of sample j on every lane, and raw in C layout
-// (register v = raw output 4g + v of sample j).
+// The density MLP on a 16-sample tile: raw outputs in C layout (register v =
+// raw output 4g + v of sample j).  fe: this lane's features (its level group,
+// its sample); W: fragments in LDS (only the two density layers are read).
 template <int NL, int SH, int CL, bool BF>
-__device__ __forceinline__ void mlp_tile(const uint32_t* __restrict__ W, const float* fe, const float (&u)[4][4],
-                                         float density_offset, int lane, float& sigma, float rgb[3], f4v& raw) {
+__device__ __forceinline__ f4v density_raw(const uint32_t* __restrict__ W, const float* fe, int lane) {
   using LY = FragLayout<NL, SH, CL, BF>;
-  const int g = lane >> 4, j = lane & 15;
   const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
   // density layer 1: 64 hidden x 16 samples
   f4v h[4] = {zero, zero, zero, zero};
@@ -276,7 +272,21 @@ __device__ __forceinline__ void mlp_tile(const uint32_t* __restrict__ W, const f
       }
     }
   }
-  raw = rp[0] + rp[1];
+  return rp[0] + rp[1];
+}
+
+// The MLPs on a 16-sample tile.  fe: this lane's features (its level group,
+// its sample); u[mt][v]: the colour layer-1 contribution of the SH inputs for
+// hidden row mt*16 + 4g + v (per lane's sample); W: fragments in LDS.
+// Returns sigma and rgb of sample j on every lane, and raw in C layout
+// (register v = raw output 4g + v of sample j).
+template <int NL, int SH, int CL, bool BF>
+__device__ __forceinline__ void mlp_tile(const uint32_t* __restrict__ W, const float* fe, const float (&u)[4][4],
+                                         float density_offset, int lane, float& sigma, float rgb[3], f4v& raw) {
+  using LY = FragLayout<NL, SH, CL, BF>;
+  const int g = lane >> 4, j = lane & 15;
+  const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  raw = density_raw<NL, SH, CL, BF>(W, fe, lane);
   sigma = softplusf(__shfl(raw[0], j, 64) + density_offset);
   // colour layer 1: SH part precomputed in u, raw part on the matrix cores
   f4v c[4];
