@@ -111,12 +111,8 @@ __global__ void k_init(int64_t n, const float* __restrict__ o, const float* __re
                        const int32_t* __restrict__ per_ray_mb, int max_bounces, RayQueue q, int* __restrict__ counts,
                        int n_counts, int32_t* __restrict__ hit_ids, int hit_stride, unsigned long long* __restrict__ stats) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid == 0) {
-    for (int k = 0; k < n_counts; ++k) counts[k] = 0;
-    counts[0] = (int)n;
-    if (stats)
-      for (int k = 0; k < 4; ++k) stats[k] = 0ull;
-  }
+  for (int64_t k = tid; k < n_counts; k += (int64_t)gridDim.x * blockDim.x) counts[k] = k == 0 ? (int)n : 0;
+  if (stats && tid < 4) stats[tid] = 0ull;
   for (int64_t i = tid; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     q.ox[i] = o[3 * i]; q.oy[i] = o[3 * i + 1]; q.oz[i] = o[3 * i + 2];
     q.dx[i] = d[3 * i]; q.dy[i] = d[3 * i + 1]; q.dz[i] = d[3 * i + 2];
