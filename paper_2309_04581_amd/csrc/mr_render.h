@@ -77,15 +77,6 @@ struct ShadeParams {
   int sample_emitters;   // light sampling toward the mesh's emitting triangles
 };
 
-// The medium a light sample's shadow segment crosses (light sampling toward
-// emitters): the fields of the render and the spacing of the march's grid.
-struct ShadowMedium {
-  int n;                        // fields (0: the light sample sees no medium)
-  float delta;                  // grid spacing (t_far - t_near) / n_samples
-  int use_occupancy;
-  FieldView f[kMaxFields];
-};
-
 // Ray queue depth word: bits 0-15 segment index (= scatter count so far),
 // bits 16-23 the ray's bounce limit, bit 24 set when the last scatter was
 // diffuse.
@@ -98,6 +89,11 @@ struct RenderOut {
 };
 
 constexpr int kXcds = 8;               // accelerator complex dies; workgroups go round-robin over them
+
+// Counters in the workspace header: live rays, closest-hit and shade queue
+// heads and kXcds march queue heads per segment, the march waits that gave up,
+// and a light-sample queue head per segment.
+constexpr int kHeaderCounters = (4 + kXcds) * (kMaxBounces + 2) + 1;
 
 // Ray work queue of the persistent march kernels.  chunk == 0: one queue for
 // the whole device.  chunk > 0: the rays [0, cnt) are cut into chunks of
@@ -156,6 +152,18 @@ mr_status dispatch_march_mfma(const mr_field* f, RayQueue q, const int* count, i
 mr_status dispatch_march_fields(const mr_field* const* fields, int n_fields, RayQueue q, const int* count, int* work,
                                 const MarchParams& P, const BvhView& B, bool packets, unsigned long long* stats,
                                 int blocks_per_cu, int64_t n, hipStream_t st);
+
+// Medium of the light samples toward emitters (light_march.hip).  The shade
+// pass leaves a light sample's record in the slot of the ray it shaded, in the
+// queue it has read: origin and direction of the shadow segment, its length in
+// hit_t, the light it carries in tr tg tb, the optical depth so far (0) in lr,
+// where the light goes in rid (s >= 0: the ray in slot s of the next queue,
+// ~i: the finished caller's ray i) and kLightPending in hit_p.  One launch per
+// field adds that field's depth; the last one adds the light times the
+// transmittance to the ray.  work: a zeroed counter, or null for a fixed split.
+constexpr int kLightPending = 1;
+mr_status dispatch_light_march(const mr_field* f, RayQueue q, RayQueue next, const int* count, int* work, float delta,
+                               bool use_occupancy, bool last, float* radiance, int64_t n, hipStream_t st);
 
 // proposal-sampled march (defined with the proposal kernels)
 // packets: 16 consecutive queue rays per wave when n_prop = 32 and n_fine <= 32

@@ -177,101 +177,16 @@ __device__ __forceinline__ void finalize(const RenderOut& out, int rid, float tr
   out.bounces[rid] = bounces;
 }
 
-// Optical depth of one field along [0, len] of the world ray so + t sd: the
-// density at the midpoints of the march's grid intervals (spacing delta from
-// t = 0), each clipped to the segment and the field's box, times their
-// lengths; samples in empty occupancy cells count zero.  The density MLP's
-// first layer is accumulated level by level (64 hidden sums, the weights read
-// at uniform addresses), so one thread holds about a hundred registers.
-template <int NL, typename TabT>
-__device__ float field_depth(const FieldView& F, const TabT* __restrict__ tab, V3 so, V3 sd, float len, float delta,
-                             bool occ) {
-  float ox = so.x, oy = so.y, oz = so.z, dx = sd.x, dy = sd.y, dz = sd.z;
-  to_field_frame(F, ox, oy, oz, dx, dy, dz);
-  float b0, b1;
-  if (!slab_box(F, ox, oy, oz, dx, dy, dz, b0, b1)) return 0.0f;
-  const float lo = fmaxf(0.0f, b0), hi = fminf(len, b1);
-  if (!(hi > lo)) return 0.0f;
-  const size_t T = (size_t)F.table_mask + 1u;
-  // the weights are constant for the kernel and read at wave-uniform
-  // addresses: through the constant address space they are scalar loads
-  typedef const __attribute__((address_space(4))) float* ConstF;
-  const ConstF W0 = (ConstF)F.mlp;               // [64][32]
-  const ConstF W1 = (ConstF)(F.mlp + 2048);      // row 0 of [16][64]
-  float tau = 0.0f;
-  // the intervals that meet [lo, hi], started one early so that FP32 rounding
-  // of k delta cannot skip the first; at most 2^20 per field (a box 2^20 grid
-  // intervals across), so the loop is bounded (indices clamped below 2^40)
-  const float kf0 = fminf(fmaxf(0.0f, floorf(lo / delta) - 1.0f), 1.0995e12f);
-  const float kf1 = fminf(ceilf(hi / delta) + 1.0f, kf0 + (float)(1 << 20));
-  const int64_t k0 = (int64_t)kf0, k1 = (int64_t)kf1;
-#pragma unroll 1
-  for (int64_t k = k0; k <= k1; ++k) {
-    float a = (float)k * delta, b = (float)(k + 1) * delta;
-    if (b <= lo) continue;
-    if (a >= hi) break;
-    a = fmaxf(a, lo);
-    b = fminf(b, hi);
-    const float tm = 0.5f * (a + b);
-    const float px = ox + tm * dx, py = oy + tm * dy, pz = oz + tm * dz;
-    if (occ && !occ_lookup(F, px, py, pz)) continue;
-    float xh, yh, zh;
-    to_unit(F, px, py, pz, xh, yh, zh);
-    float h[64];
-#pragma unroll
-    for (int j = 0; j < 64; ++j) h[j] = 0.0f;
-#pragma unroll 1
-    for (int l = 0; l < NL; ++l) {
-      uint32_t idx[8];
-      float w[8];
-      level_corners(F, l, xh, yh, zh, idx, w);
-      const TabT* t = tab + (size_t)l * T * 2;
-      float f0 = 0.0f, f1 = 0.0f;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float2 e = load_entry<TabT>(t, idx[c]);
-        f0 += w[c] * e.x;
-        f1 += w[c] * e.y;
-      }
-#pragma unroll
-      for (int j = 0; j < 64; ++j) h[j] += W0[j * 32 + 2 * l] * f0 + W0[j * 32 + 2 * l + 1] * f1;
-    }
-    float r = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 64; ++j) r += W1[j] * fmaxf(h[j], 0.0f);
-    tau += softplusf(r + F.density_offset) * (b - a);
-  }
-  return tau;
-}
-
-// Transmittance of the medium along a light sample's shadow segment (the sum
-// of the fields' optical depths): the light the sample carries crosses it, as
-// a bounce that reaches the emitter is attenuated by its own march.
-__device__ float shadow_transmittance(const ShadowMedium& SM, V3 so, V3 sd, float len) {
-  float tau = 0.0f;
-  for (int k = 0; k < SM.n; ++k) {
-    const FieldView& F = SM.f[k];
-    const bool occ = SM.use_occupancy && F.occ;
-    if (F.n_levels == 16)
-      tau += F.table_h ? field_depth<16, __half>(F, F.table_h, so, sd, len, SM.delta, occ)
-                       : field_depth<16, float>(F, F.table, so, sd, len, SM.delta, occ);
-    else
-      tau += F.table_h ? field_depth<8, __half>(F, F.table_h, so, sd, len, SM.delta, occ)
-                       : field_depth<8, float>(F, F.table, so, sd, len, SM.delta, occ);
-  }
-  return expf(-tau);
-}
-
-// MEDIUM: light samples toward emitters are attenuated by the fields in SM
-// (only launched with light sampling and a medium; the other instance
-// carries none of that code).
+// MEDIUM: a light sample toward an emitter crosses the render's fields before
+// it reaches the ray: its record is left in the ray's slot of the queue just
+// read, for dispatch_light_march (only launched with light sampling and a
+// medium).
 template <bool MEDIUM>
 __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* __restrict__ count_in,
                                                        int* __restrict__ work, int tile, RayQueue qo,
                                                        int* __restrict__ count_out, MeshView M, ShadeParams S,
                                                        RenderOut out, float span, int32_t* __restrict__ hit_ids,
-                                                       int hit_stride, unsigned long long* __restrict__ stats,
-                                                       ShadowMedium SM) {
+                                                       int hit_stride, unsigned long long* __restrict__ stats) {
   __shared__ int stack[kStack * kTraceBlock];
   __shared__ float tstack[kStack * kTraceBlock];
   __shared__ int s_base;
@@ -287,7 +202,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
   const int tend = min(tbase + tile, cnt);
   for (int i0 = tbase; i0 < tend; i0 += blockDim.x) {
     const int i = i0 + threadIdx.x;
-    bool keep = false;
+    bool keep = false, light = false;
     float nox = 0, noy = 0, noz = 0, ndx = 0, ndy = 0, ndz = 0, tr = 0, tg = 0, tb = 0, lr = 0, lg = 0, lb = 0;
     int rid = 0, ndepth = 0;
     if (i < tend) {
@@ -374,11 +289,21 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
               ++n_shadow;
               if (bvh_trace<true>(M.bvh, sr, (1.0f - 1e-3f) * sdist, th, stack + threadIdx.x, nullptr, kTraceBlock) < 0) {
                 const Material& em = M.mat[__float_as_int(a1.w)];
-                float g = cos_p * cos_x / d2 * (0.5f * a2x) / e.y * (1.0f / 3.14159265358979323846f);
-                if constexpr (MEDIUM) g *= shadow_transmittance(SM, so, sd, sdist);
-                lr += tr * mat.albedo[0] * em.emission[0] * g;
-                lg += tg * mat.albedo[1] * em.emission[1] * g;
-                lb += tb * mat.albedo[2] * em.emission[2] * g;
+                const float g = cos_p * cos_x / d2 * (0.5f * a2x) / e.y * (1.0f / 3.14159265358979323846f);
+                const float cr = tr * mat.albedo[0] * em.emission[0] * g, cg = tg * mat.albedo[1] * em.emission[1] * g,
+                            cb = tb * mat.albedo[2] * em.emission[2] * g;
+                if constexpr (MEDIUM) {
+                  light = true;
+                  qi.ox[i] = so.x; qi.oy[i] = so.y; qi.oz[i] = so.z;
+                  qi.dx[i] = sd.x; qi.dy[i] = sd.y; qi.dz[i] = sd.z;
+                  qi.hit_t[i] = sdist;
+                  qi.tr[i] = cr; qi.tg[i] = cg; qi.tb[i] = cb;
+                  qi.lr[i] = 0.0f;
+                } else {
+                  lr += cr;
+                  lg += cg;
+                  lb += cb;
+                }
               }
             }
           }
@@ -454,8 +379,13 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
     int base = 0;
     if (lane == 0 && nk) base = atomicAdd(count_out, nk);
     base = __shfl(base, 0, 64);
+    const int slot = base + __popcll(m & ((1ull << lane) - 1ull));
+    if constexpr (MEDIUM)
+      if (i < tend) {
+        qi.hit_p[i] = light ? kLightPending : 0;
+        qi.rid[i] = keep ? slot : ~rid;
+      }
     if (keep) {
-      const int slot = base + __popcll(m & ((1ull << lane) - 1ull));
       qo.ox[slot] = nox; qo.oy[slot] = noy; qo.oz[slot] = noz;
       qo.dx[slot] = ndx; qo.dy[slot] = ndy; qo.dz[slot] = ndz;
       qo.tr[slot] = tr; qo.tg[slot] = tg; qo.tb[slot] = tb;
@@ -841,7 +771,7 @@ extern "C" size_t mr_render_workspace_size(int64_t n) {
 // counters (kXcds per field) and the per-field scratch T and L arrays
 static constexpr size_t kFieldCtrBytes = 256;
 static_assert(kMaxFields * kXcds * sizeof(int) <= kFieldCtrBytes, "field counters");
-static_assert(((3 + kXcds) * (kMaxBounces + 2) + 1) * sizeof(int) <= kHeaderBytes, "workspace header");
+static_assert(kHeaderCounters * sizeof(int) <= kHeaderBytes, "workspace header");
 
 extern "C" size_t mr_render_fields_workspace_size(int64_t n, int32_t n_fields) {
   const int64_t cap = ((std::max<int64_t>(n, 1) + 63) / 64) * 64;
@@ -922,6 +852,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   int* swork = twork + (kMaxBounces + 2);                   // shade tile queue heads
   int* work = swork + (kMaxBounces + 2);                    // march: kXcds ray queue heads per segment
   int* gave_up = work + kXcds * (kMaxBounces + 2);          // march waits that gave up (mr_render_status)
+  int* lwork = gave_up + 1;                                 // light-sample march: a queue head per segment
   RayQueue Q[2] = {queue_at(ws + kHeaderBytes, cap), queue_at(ws + kHeaderBytes + queue_bytes(cap), cap)};
   int* fctr = reinterpret_cast<int*>(ws + mr_render_workspace_size(n));     // several fields only
   float* fscratch = reinterpret_cast<float*>(ws + mr_render_workspace_size(n) + kFieldCtrBytes);
@@ -941,7 +872,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
 
   const int init_blocks = (int)std::min<int64_t>((n + 255) / 256, 65535);
   hipLaunchKernelGGL(k_init, dim3(init_blocks), dim3(256), 0, st, n, origins, dirs, per_ray_max_bounces, max_bounces,
-                     Q[0], counts, (3 + kXcds) * (kMaxBounces + 2) + 1, out->hit_ids, out->hit_ids ? out->hit_stride : 0,
+                     Q[0], counts, kHeaderCounters, out->hit_ids, out->hit_ids ? out->hit_stride : 0,
                      stats);
   MR_HIP(hipGetLastError());
 
@@ -981,14 +912,8 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   S.sample_emitters = opts->sample_emitters ? 1 : 0;
 
   // light samples toward emitters cross the render's fields
-  ShadowMedium SM;
-  std::memset(&SM, 0, sizeof(SM));
-  if (S.sample_emitters && mesh && mv.n_emit > 0) {
-    SM.delta = opts->light_depth_samples > 0 ? P.span / (float)opts->light_depth_samples : P.delta;
-    SM.use_occupancy = opts->use_occupancy;
-    for (int k = 0; k < n_fields; ++k)
-      if (fields[k]) SM.f[SM.n++] = fields[k]->view;
-  }
+  const bool light_medium = S.sample_emitters && mesh && mv.n_emit > 0 && n_fields > 0 && fields[0];
+  const float light_delta = opts->light_depth_samples > 0 ? P.span / (float)opts->light_depth_samples : P.delta;
 
   RenderOut ro;
   ro.radiance = out->radiance;
@@ -1054,15 +979,16 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
     }
     {
       StageTimer tm(2, st, timed);
-      if (SM.n > 0)
-        hipLaunchKernelGGL(k_shade<true>, dim3(shade_blocks), dim3(kTraceBlock), 0, st, qi, counts + b, swork + b, tile,
-                           qo, counts + b + 1, mv, S, ro, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats,
-                           SM);
-      else
-        hipLaunchKernelGGL(k_shade<false>, dim3(shade_blocks), dim3(kTraceBlock), 0, st, qi, counts + b, swork + b, tile,
-                           qo, counts + b + 1, mv, S, ro, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats,
-                           SM);
+      auto* k = light_medium ? k_shade<true> : k_shade<false>;
+      hipLaunchKernelGGL(k, dim3(shade_blocks), dim3(kTraceBlock), 0, st, qi, counts + b, swork + b, tile, qo,
+                         counts + b + 1, mv, S, ro, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
       MR_HIP(hipGetLastError());
+      // no light sample on a ray's last segment
+      for (int k = 0; light_medium && b < max_bounces && k < n_fields; ++k) {
+        s = dispatch_light_march(fields[k], qi, qo, counts + b, k == 0 ? lwork + b : nullptr, light_delta,
+                                 opts->use_occupancy != 0, k + 1 == n_fields, ro.radiance, n, st);
+        if (s != MR_OK) return s;
+      }
     }
     if (b < max_bounces) {
       // closest hits of the next segment when this queue is short (the kernel
