@@ -276,7 +276,11 @@ typedef struct {
   int64_t* counters;         /* optional device int64[4]: samples, segments, shadow rays, scatters */
 } mr_render_out;
 
-/* Bytes of device workspace mr_render needs for n rays. */
+/* Bytes of device workspace for n rays: the ray queues and, for 65 536 rays
+ * or more, 256 MiB (at 256 compute units) in which bounce rays through a
+ * 16-level field are marched one hash level at a time.  mr_render also takes
+ * a workspace of the queues alone (4096 + 128 n bytes, n rounded up to 64)
+ * and then marches them ray by ray: the same results, more slowly. */
 size_t mr_render_workspace_size(int64_t n);
 
 /* Render n rays: origins, dirs (n, 3) device, unit directions.

@@ -18,35 +18,11 @@
 #include <vector>
 
 #include "mr_field_kernels.h"
-#include "mr_mfma.h"
-#include "mr_render.h"
+#include "mr_march.h"
 
 using namespace mr;
 
 namespace {
-
-// A ray's segment in the field: origin and direction in the field frame,
-// the range [lo, hi] it marches and the sample indices k0 .. k1 that cover it.
-struct RaySeg {
-  float ox, oy, oz, dx, dy, dz, t_a, lo, hi;
-  int k0, k1;
-};
-
-__device__ __forceinline__ bool ray_seg(const RayQueue& q, int r, const FieldView& F, const MarchParams& P,
-                                        RaySeg& S) {
-  S.ox = q.ox[r]; S.oy = q.oy[r]; S.oz = q.oz[r];
-  S.dx = q.dx[r]; S.dy = q.dy[r]; S.dz = q.dz[r];
-  to_field_frame(F, S.ox, S.oy, S.oz, S.dx, S.dy, S.dz);
-  S.t_a = (q.depth[r] & 0xFFFF) == 0 ? P.t_near : 0.0f;
-  float box0, box1;
-  if (!slab_box(F, S.ox, S.oy, S.oz, S.dx, S.dy, S.dz, box0, box1)) return false;
-  S.lo = fmaxf(S.t_a, box0);
-  S.hi = fminf(fminf(S.t_a + P.span, q.hit_t[r]), box1);
-  if (!(S.hi > S.lo)) return false;
-  S.k0 = max(0, (int)floorf((S.lo - S.t_a) / P.delta) - 1);
-  S.k1 = min(P.n_samples, (int)ceilf((S.hi - S.t_a) / P.delta) + 1);
-  return true;
-}
 
 // Samples kb0 .. kb1 - 1 of the segment, one wave: lane j takes sample kb + j
 // of each 16-sample tile, and transmittance is a 16-lane prefix product
@@ -87,16 +63,6 @@ __device__ __forceinline__ void march_tiles(const RaySeg& S, int kb0, int kb1, c
     Tseg *= __shfl(incl, 15, 16);
     if (g == 0 && valid) ++nsamp;
   }
-}
-
-__device__ __forceinline__ void ray_update(const RayQueue& q, int r, float T, float l0, float l1, float l2) {
-  const float tr = q.tr[r], tg = q.tg[r], tb = q.tb[r];
-  q.lr[r] += tr * l0;
-  q.lg[r] += tg * l1;
-  q.lb[r] += tb * l2;
-  q.tr[r] = tr * T;
-  q.tg[r] = tg * T;
-  q.tb[r] = tb * T;
 }
 
 // One ray per wave, all of its tiles in order.
@@ -269,6 +235,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     RayQueue q, const int* __restrict__ count, int* __restrict__ work, FieldView F, const TabT* __restrict__ table,
     const uint32_t* __restrict__ frags, MarchParams P, BvhView B, unsigned long long* __restrict__ stats) {
   using LY = FragLayout<NL, SH, CL, BF>;
+  if (P.lv && *count >= kLvMinRays) return;   // k_march_lv takes a long queue
   __shared__ __align__(16) uint32_t sW[LY::TOTAL];
   __shared__ int sstack[4 * 16 * kStack];   // shadow-ray stacks: 16 lanes per wave
   for (int i = threadIdx.x; i < LY::TOTAL; i += blockDim.x) sW[i] = frags[i];

@@ -204,6 +204,91 @@ __device__ __forceinline__ void encode_level(const FieldView& F, const TabT* __r
   }
 }
 
+// One level for the wave's 64 samples, a sample per lane, for loops that keep
+// the whole machine on one level at a time.  Two neighbouring lanes share
+// their loads: each instruction fetches the two x corners of one sample of the
+// pair, lane 2i the corner at x and lane 2i + 1 the one at x + 1, which lie in
+// one 128-byte line 15 times of 16 (the table's x prime is 1), so an
+// instruction touches half the lines that a sample per lane would (random
+// points, one 4 MiB level in L2: 22 against 30 ps per sample).  Every lane then
+// takes its own sample's corners from the pair and sums them in the order of
+// encode_level: the same bits.  All lanes of the wave must be active.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t pair_get(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xF, 0xF, true);
+}
+constexpr int kPairEven = 0xA0, kPairOdd = 0xF5;   // quad_perm [0,0,2,2] and [1,1,3,3]
+
+// Entry at a byte offset within one level's slice.
+template <typename TabT>
+__device__ __forceinline__ float2 load_at(const TabT* __restrict__ tab, uint32_t byte) {
+  return load_entry<TabT>(reinterpret_cast<const TabT*>(reinterpret_cast<const char*>(tab) + byte), 0u);
+}
+
+template <typename TabT>
+__device__ __forceinline__ float2 encode_level_pair(const FieldView& F, const TabT* __restrict__ table, int l, int lane,
+                                                    float xh, float yh, float zh) {
+  constexpr int kShift = sizeof(TabT) == 4 ? 3 : 2;   // log2 of an entry's bytes
+  const TabT* tab = table + (size_t)l * ((size_t)F.table_mask + 1u) * 2;
+  const int N = F.res[l];
+  const float fN = (float)N, top = fN - 1.0f;
+  const float fx = xh * fN, fy = yh * fN, fz = zh * fN;
+  const float flx = fminf(floorf(fx), top), fly = fminf(floorf(fy), top), flz = fminf(floorf(fz), top);
+  const uint32_t vx = (uint32_t)flx, vy = (uint32_t)fly, vz = (uint32_t)flz;
+  const float wx = fx - flx, wy = fy - fly, wz = fz - flz;
+  const bool odd = lane & 1;
+  const uint32_t xe = pair_get<kPairEven>(vx) + (odd ? 1u : 0u), xo = pair_get<kPairOdd>(vx) + (odd ? 1u : 0u);
+  uint32_t oe[4], oo[4];   // the even and the odd lane's sample
+  if ((F.dense_mask >> l) & 1u) {
+    const uint32_t n1 = (uint32_t)N + 1u, n2 = n1 * n1;
+    const uint32_t b = vy * n1 + vz * n2;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t y = b + (c & 1) * n1 + (c >> 1) * n2;
+      oe[c] = (xe + pair_get<kPairEven>(y)) << kShift;
+      oo[c] = (xo + pair_get<kPairOdd>(y)) << kShift;
+    }
+  } else {
+    // only the low bits of the products are kept (the table has at most 2^24
+    // entries and N is at most 2^20), so 24-bit multiplies serve
+    const uint32_t py = 2654435761u & F.table_mask, pz = 805459861u & F.table_mask;
+    const uint32_t hy = __umul24(vy, py), hz = __umul24(vz, pz);
+    const uint32_t me = xe & F.table_mask, mo = xo & F.table_mask;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t y = ((hy + (c & 1) * py) ^ (hz + (c >> 1) * pz)) & F.table_mask;
+      oe[c] = (me ^ pair_get<kPairEven>(y)) << kShift;
+      oo[c] = (mo ^ pair_get<kPairOdd>(y)) << kShift;
+    }
+  }
+  float2 ee[4], eo[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) ee[c] = load_at<TabT>(tab, oe[c]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) eo[c] = load_at<TabT>(tab, oo[c]);
+  float f0 = 0.0f, f1 = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    // x corner: the even lane's load for the even sample, for the odd sample
+    // what the even lane fetched for it; x + 1 likewise from the odd lane
+    const float2 a = ee[c >> 1], b = eo[c >> 1];
+    float ex, ey;
+    if (c & 1) {
+      const uint32_t ax = pair_get<kPairOdd>(__float_as_uint(a.x)), ay = pair_get<kPairOdd>(__float_as_uint(a.y));
+      ex = odd ? b.x : __uint_as_float(ax);
+      ey = odd ? b.y : __uint_as_float(ay);
+    } else {
+      const uint32_t bx = pair_get<kPairEven>(__float_as_uint(b.x)), by = pair_get<kPairEven>(__float_as_uint(b.y));
+      ex = odd ? __uint_as_float(bx) : a.x;
+      ey = odd ? __uint_as_float(by) : a.y;
+    }
+    const float w = ((c & 1) ? wx : 1.0f - wx) * ((c & 2) ? wy : 1.0f - wy) * ((c & 4) ? wz : 1.0f - wz);
+    f0 += w * ex;
+    f1 += w * ey;
+  }
+  return make_float2(f0, f1);
+}
+
 // The density MLP on a 16-sample tile: raw outputs in C layout (register v =
 // raw output 4g + v of sample j).  fe: this lane's features (its level group,
 // its sample); W: fragments in LDS (only the two density layers are read).

@@ -39,6 +39,7 @@ struct MarchParams {
   // rays are then left without this segment's medium)
   int wait_polls;
   int* gave_up;
+  int lv;             // queues of kLvMinRays or more are marched by k_march_lv
 };
 
 // Shadow mask of the sample of column j (Sec. 3.1 "Shadow rays"): a lane of
@@ -164,6 +165,29 @@ mr_status dispatch_march_fields(const mr_field* const* fields, int n_fields, Ray
 constexpr int kLightPending = 1;
 mr_status dispatch_light_march(const mr_field* f, RayQueue q, RayQueue next, const int* count, int* work, float delta,
                                bool use_occupancy, bool last, float* radiance, int64_t n, hipStream_t st);
+
+// march of incoherent segments level by level (march_lv.hip); it leaves queues
+// of fewer than kLvMinRays rays alone.  Its scratch in the workspace: kLvPaceArea
+// bytes of pacing counters, kLvPaceInts for each launch and zeroed with the
+// header, then the features of the blocks' batches.
+constexpr int kLvSamples = 4096;   // samples per batch
+// Below this queue length the per-ray march is as fast (mid frames of 128 to
+// 800 pixels a side); frames of fewer than kLvMinFrame rays hardly have such
+// queues after their first bounce and carry no scratch.
+constexpr int kLvMinRays = 8192;
+constexpr int64_t kLvMinFrame = 65536;
+constexpr int kLvLine = 32;        // words between two counters: a 128-byte line each
+constexpr int kLvPaceInts = kXcds * 4 * kLvLine;
+constexpr size_t kLvPaceArea = (size_t)(kMaxBounces + 2) * kLvPaceInts * sizeof(int);
+struct LvScratch {
+  int* pace;      // this launch's counters
+  double* feat;   // (feature 0, feature 1) pairs
+};
+int lv_blocks();
+size_t lv_bytes();
+bool lv_field(const mr_field* f);
+mr_status dispatch_march_lv(const mr_field* f, RayQueue q, const int* count, int* work, const MarchParams& P,
+                            const LvScratch& lv, unsigned long long* stats, hipStream_t st);
 
 // proposal-sampled march (defined with the proposal kernels)
 // packets: 16 consecutive queue rays per wave when n_prop = 32 and n_fine <= 32

@@ -109,9 +109,11 @@ __device__ __forceinline__ V3 face_normal(V3 a, V3 b) {
 // ---------------------------------------------------------------------------
 __global__ void k_init(int64_t n, const float* __restrict__ o, const float* __restrict__ d,
                        const int32_t* __restrict__ per_ray_mb, int max_bounces, RayQueue q, int* __restrict__ counts,
-                       int n_counts, int32_t* __restrict__ hit_ids, int hit_stride, unsigned long long* __restrict__ stats) {
+                       int n_counts, int* __restrict__ pace, int n_pace, int32_t* __restrict__ hit_ids, int hit_stride,
+                       unsigned long long* __restrict__ stats) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t k = tid; k < n_counts; k += (int64_t)gridDim.x * blockDim.x) counts[k] = k == 0 ? (int)n : 0;
+  for (int64_t k = tid; k < n_pace; k += (int64_t)gridDim.x * blockDim.x) pace[k] = 0;
   if (stats && tid < 4) stats[tid] = 0ull;
   for (int64_t i = tid; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     q.ox[i] = o[3 * i]; q.oy[i] = o[3 * i + 1]; q.oz[i] = o[3 * i + 2];
@@ -762,21 +764,26 @@ mr_status validate_render(const mr_field* field, const mr_mesh* mesh, int64_t n,
 
 }  // namespace mr
 
-extern "C" size_t mr_render_workspace_size(int64_t n) {
-  const int64_t cap = ((std::max<int64_t>(n, 1) + 63) / 64) * 64;
-  return kHeaderBytes + 2 * queue_bytes(cap);
-}
-
 // several fields: after the single-field workspace, 256 bytes of march
 // counters (kXcds per field) and the per-field scratch T and L arrays
 static constexpr size_t kFieldCtrBytes = 256;
 static_assert(kMaxFields * kXcds * sizeof(int) <= kFieldCtrBytes, "field counters");
 static_assert(kHeaderCounters * sizeof(int) <= kHeaderBytes, "workspace header");
 
-extern "C" size_t mr_render_fields_workspace_size(int64_t n, int32_t n_fields) {
+// Ray queues, and the scratch of several fields; the level-by-level march's
+// scratch follows (a workspace without it is accepted and marched without).
+static size_t queues_bytes(int64_t n, int32_t n_fields) {
   const int64_t cap = ((std::max<int64_t>(n, 1) + 63) / 64) * 64;
-  if (n_fields <= 1) return mr_render_workspace_size(n);
-  return mr_render_workspace_size(n) + kFieldCtrBytes + (size_t)n_fields * 6 * sizeof(float) * (size_t)cap;
+  const size_t q = kHeaderBytes + 2 * queue_bytes(cap);
+  return n_fields <= 1 ? q : q + kFieldCtrBytes + (size_t)n_fields * 6 * sizeof(float) * (size_t)cap;
+}
+
+extern "C" size_t mr_render_workspace_size(int64_t n) {
+  return queues_bytes(n, 1) + (n >= kLvMinFrame ? lv_bytes() : 0);
+}
+
+extern "C" size_t mr_render_fields_workspace_size(int64_t n, int32_t n_fields) {
+  return n_fields <= 1 ? mr_render_workspace_size(n) : queues_bytes(n, n_fields);
 }
 
 namespace {
@@ -840,7 +847,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   mr_status s = MR_OK;
   const mr_field* field = n_fields == 1 ? fields[0] : nullptr;
   if (n == 0) return MR_OK;
-  if (!workspace || workspace_bytes < mr_render_fields_workspace_size(n, n_fields))
+  if (!workspace || workspace_bytes < queues_bytes(n, n_fields))
     return fail(MR_ERR_INVALID_ARG, n_fields > 1 ? "workspace smaller than mr_render_fields_workspace_size(n, n_fields)"
                                                  : "workspace smaller than mr_render_workspace_size(n)");
   if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(MR_ERR_INVALID_ARG, "workspace not 256-byte aligned");
@@ -854,8 +861,8 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   int* gave_up = work + kXcds * (kMaxBounces + 2);          // march waits that gave up (mr_render_status)
   int* lwork = gave_up + 1;                                 // light-sample march: a queue head per segment
   RayQueue Q[2] = {queue_at(ws + kHeaderBytes, cap), queue_at(ws + kHeaderBytes + queue_bytes(cap), cap)};
-  int* fctr = reinterpret_cast<int*>(ws + mr_render_workspace_size(n));     // several fields only
-  float* fscratch = reinterpret_cast<float*>(ws + mr_render_workspace_size(n) + kFieldCtrBytes);
+  int* fctr = reinterpret_cast<int*>(ws + queues_bytes(n, 1));     // several fields only
+  float* fscratch = reinterpret_cast<float*>(ws + queues_bytes(n, 1) + kFieldCtrBytes);
   FieldBoxes FB;
   std::memset(&FB, 0, sizeof(FB));
   FB.n = n_fields > 1 ? n_fields : 0;
@@ -869,12 +876,6 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
     }
   }
   unsigned long long* stats = reinterpret_cast<unsigned long long*>(out->counters);
-
-  const int init_blocks = (int)std::min<int64_t>((n + 255) / 256, 65535);
-  hipLaunchKernelGGL(k_init, dim3(init_blocks), dim3(256), 0, st, n, origins, dirs, per_ray_max_bounces, max_bounces,
-                     Q[0], counts, kHeaderCounters, out->hit_ids, out->hit_ids ? out->hit_stride : 0,
-                     stats);
-  MR_HIP(hipGetLastError());
 
   MeshView mv;
   std::memset(&mv, 0, sizeof(mv));
@@ -897,6 +898,18 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
     for (int k = 0; k < 3; ++k) P.light_pos[i][k] = host_lights[i].pos[k];
   P.wait_polls = opts->wait_polls;
   P.gave_up = gave_up;
+  // per-ray segments of a large 16-level field go level by level where the
+  // workspace has the scratch area for it
+  int* lv_pace = reinterpret_cast<int*>(ws + queues_bytes(n, n_fields));
+  double* lv_feat = reinterpret_cast<double*>(reinterpret_cast<char*>(lv_pace) + kLvPaceArea);
+  P.lv = n_fields == 1 && opts->sampler == MR_SAMPLER_UNIFORM && !P.shadows && n >= kLvMinFrame &&
+         workspace_bytes >= queues_bytes(n, n_fields) + lv_bytes() && lv_field(field);
+
+  const int init_blocks = (int)std::min<int64_t>((n + 255) / 256, 65535);
+  hipLaunchKernelGGL(k_init, dim3(init_blocks), dim3(256), 0, st, n, origins, dirs, per_ray_max_bounces, max_bounces,
+                     Q[0], counts, kHeaderCounters, lv_pace, P.lv ? (max_bounces + 1) * kLvPaceInts : 0,
+                     out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
+  MR_HIP(hipGetLastError());
 
   ShadeParams S;
   std::memset(&S, 0, sizeof(S));
@@ -972,9 +985,17 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
       if (opts->sampler == MR_SAMPLER_PROPOSAL)
         s = dispatch_march_proposal(field, opts->proposal, qi, counts + b, work + kXcds * b, P, mv.bvh, opts->n_proposal,
                                     opts->n_fine, b < packet_segments, stats, opts->march_blocks_per_cu, n, st);
-      else
-        s = dispatch_march_mfma(field, qi, counts + b, work + kXcds * b, P, mv.bvh, b < packet_segments, stats,
+      else {
+        if (P.lv && b >= packet_segments) {
+          s = dispatch_march_lv(field, qi, counts + b, work + kXcds * b, P, {lv_pace + kLvPaceInts * b, lv_feat}, stats,
+                                st);
+          if (s != MR_OK) return s;
+        }
+        MarchParams Pb = P;
+        Pb.lv = P.lv && b >= packet_segments;
+        s = dispatch_march_mfma(field, qi, counts + b, work + kXcds * b, Pb, mv.bvh, b < packet_segments, stats,
                                 opts->march_blocks_per_cu, n, st);
+      }
       if (s != MR_OK) return s;
     }
     {

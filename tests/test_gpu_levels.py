@@ -1,0 +1,71 @@
+"""Bounce rays marched one hash level at a time (march_lv.hip) against the
+per-ray march: a workspace of the ray queues alone turns the former off, and
+both must give the same bits."""
+import numpy as np
+import pytest
+
+from paper_2309_04581_amd import meshrf as M
+from paper_2309_04581_amd import scenegen as sg
+
+pytestmark = pytest.mark.gpu
+
+
+def _queues_bytes(n):
+    return 4096 + 128 * ((n + 63) // 64 * 64)
+
+
+def _render(F, G, o, d, sc, opts, lean):
+    R = M.Renderer(len(o), sc.max_bounces)
+    assert R.ws_bytes > _queues_bytes(len(o)), "no scratch for the level-by-level march"
+    M.mr_render(F.handle, G.handle, len(o), o, d, sc.max_bounces, None, sc.lights, opts, R.out, R.workspace,
+                _queues_bytes(len(o)) if lean else R.ws_bytes)
+    import torch
+    torch.cuda.synchronize()
+    assert R.status() == 0
+    return [t.cpu().numpy() for t in (R.radiance, R.throughput, R.bounces, R.hit_ids, R.counters)]
+
+
+# n_samples 4096: a ray fills a whole batch of 256 tiles; 3: rays of one
+# tile, far more of them than a batch has tiles; 250: ragged tiles
+@pytest.mark.parametrize("n_samples,half,occ,posed,offset", [
+    (256, False, True, False, -3.0),
+    (256, True, True, True, -3.0),
+    (250, False, False, True, 1.0),
+    (3, False, False, False, 1.0),
+    (17, True, False, False, 1.0),
+    (4096, False, True, False, -6.0),
+])
+def test_levels_match_per_ray_march(n_samples, half, occ, posed, offset):
+    import torch
+    sc = sg.mid_scene(width=331, height=257, n_samples=n_samples)   # 85 067 rays
+    sc.max_bounces = 3
+    f = sg.mid_field(9, 0.5, offset)
+    if posed:
+        f.pose = sg.pose_matrix(sg.rotation((0.3, 1.0, 0.2), 0.4), (0.1, -0.05, 0.15))
+    F = M.Field(f, **(dict(table_dtype=M.MR_F16, mlp_dtype=M.MR_BF16) if half else {}))
+    if occ:
+        F.build_occupancy(64, 0.01)
+    G = M.Mesh(sc.mesh)
+    o, d, _ = M.camera_rays(sg.cameras_array(sc.cameras))
+    opts = M.make_opts(sc, use_occupancy=occ)
+    a = _render(F, G, o, d, sc, opts, lean=False)
+    b = _render(F, G, o, d, sc, opts, lean=True)
+    assert (a[2] > 0).sum() > 8192, "too few bounce rays to leave the per-ray march"
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+    assert np.isfinite(a[0]).all()
+
+
+@pytest.mark.parametrize("log2_table,n_levels", [(17, 16), (20, 16)])
+def test_levels_of_other_table_sizes(log2_table, n_levels):
+    sc = sg.mid_scene(width=331, height=257, n_samples=96)
+    sc.max_bounces = 2
+    f = sg.make_field(n_levels=n_levels, feats=2, log2_table=log2_table, n_min=16, n_max=1024, d_hidden=64, d_out=16,
+                      c_hidden=64, c_layers=1, sh=4, seed=3, table_amp=0.5)
+    F, G = M.Field(f), M.Mesh(sc.mesh)
+    o, d, _ = M.camera_rays(sg.cameras_array(sc.cameras))
+    opts = M.make_opts(sc)
+    a = _render(F, G, o, d, sc, opts, lean=False)
+    b = _render(F, G, o, d, sc, opts, lean=True)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
