@@ -10,6 +10,7 @@
 #include "mr_device.h"
 #include "mr_field_kernels.h"
 #include "mr_mfma.h"
+#include "mr_render.h"
 
 using namespace mr;
 
@@ -36,11 +37,12 @@ uint16_t bf16_rne(float f) {
 // whose products and sums come in another order), so the tiles only decide
 // the cells they decide for certain: the two evaluations of a raw density
 // differ by at most the rounding of their sums, bounded by kOccBand times
-// max|f| sum_j |W1_j| sum_i |W0_ji| (each has about a hundred roundings of
-// 2^-24 in sequence; 2e-5 covers both three times over).  A cell whose 8
-// probes are neither one of them surely >= thresh nor all surely below it is
-// evaluated per thread.  With the vector-unit MLP on every probe the 128^3
-// grid of a 16-level field took 8.95 ms.
+// sum_j |W1_j| sum_i |W0_ji| |f_i| = sum_i a_i |f_i| (each has about a hundred
+// roundings of 2^-24 in sequence; 2e-5 covers both).  A cell whose 8 probes
+// are neither one of them surely >= thresh nor all surely below it is
+// evaluated by probe_sigma, eight lanes per cell.  With the vector-unit MLP on
+// every probe the 128^3 grid of a 16-level field took 8.95 ms; now 2.05, bound
+// by the gathers' lines from beyond L2.
 constexpr float kOccBand = 2e-5f;
 
 // sigma of one probe on one thread: every hidden sum runs over the features in
@@ -84,31 +86,37 @@ __device__ __forceinline__ void probe_point(const FieldView& F, int res, int64_t
   pz = F.amin[2] + zh * (F.amax[2] - F.amin[2]);
 }
 
-template <int NL, typename TabT>
-__global__ __launch_bounds__(256) void k_occupancy(FieldView F, const TabT* __restrict__ table,
-                                                   const uint32_t* __restrict__ frags, int res, float thresh,
-                                                   uint32_t* __restrict__ words, uint8_t* __restrict__ bytes) {
+// SHARED: the block's eight waves take one run each of the same 64 cells (a
+// grid with fewer groups of 64 cells than the device has waves: 32 tiles one
+// after the other on one wave took 126 us for a 24^3 grid).
+constexpr int kOccThreads = 512;
+
+template <int NL, typename TabT, bool SHARED>
+__global__ __launch_bounds__(kOccThreads) void k_occupancy(FieldView F, const TabT* __restrict__ table,
+                                                           const uint32_t* __restrict__ frags, int res, float thresh,
+                                                           uint32_t* __restrict__ words, uint8_t* __restrict__ bytes) {
   using LY = FragLayout<NL, 4, 1, false>;   // the density layers come first and are the same for every layout
   __shared__ __align__(16) uint32_t sW[LY::C1];
-  __shared__ float s_norm;
+  __shared__ float s_a[2 * NL];
+  __shared__ uint32_t s_run[8];
   for (int i = threadIdx.x; i < LY::C1; i += blockDim.x) sW[i] = frags[i];
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
-  if (threadIdx.x < 64) {   // sum_j |W1_j| sum_i |W0_ji| over the 64 hidden units
+  if (threadIdx.x < 2 * NL) {   // a_i
     float a = 0.0f;
-    for (int i = 0; i < 2 * NL; ++i) a += fabsf(F.mlp[lane * 32 + i]);
-    a *= fabsf(F.mlp[2048 + lane]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if (lane == 0) s_norm = a;
+    for (int h = 0; h < 64; ++h) a += fabsf(F.mlp[2048 + h]) * fabsf(F.mlp[h * 32 + threadIdx.x]);
+    s_a[threadIdx.x] = a;
   }
   __syncthreads();
-  const float norm = s_norm;
+  float ga[LY::NF];   // of this lane's features
+#pragma unroll
+  for (int k = 0; k < LY::NF; ++k) ga[k] = kOccBand * s_a[frag_k(0, LY::NF, 0, g, k)];
   const int64_t n = (int64_t)res * res * res;
-  const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
-  for (int64_t w = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); w * 64 < n; w += waves) {
+  const int wave = threadIdx.x >> 6;
+  const int64_t step = (int64_t)gridDim.x * (SHARED ? 1 : kOccThreads / 64);
+  for (int64_t w = SHARED ? blockIdx.x : (int64_t)blockIdx.x * (kOccThreads / 64) + wave; w * 64 < n; w += step) {
     uint64_t occ = 0, open = 0;   // bit i: cell 64 w + i surely occupied / undecided
 #pragma unroll 1
-    for (int run = 0; run < 8; ++run) {
+    for (int run = SHARED ? wave : 0; run < (SHARED ? wave + 1 : 8); ++run) {
       const int64_t c = min(w * 64 + run * 8 + (j >> 1), n - 1);
       bool yes = false, maybe = false;
 #pragma unroll 1
@@ -117,13 +125,13 @@ __global__ __launch_bounds__(256) void k_occupancy(FieldView F, const TabT* __re
         probe_point(F, res, c, 2 * t + (j & 1), px, py, pz);
         float fe[LY::NF];
         encode_group<NL, TabT>(F, table, px, py, pz, g, fe);
-        float fm = 0.0f;
+        float band = 0.0f;
 #pragma unroll
-        for (int k = 0; k < LY::NF; ++k) fm = fmaxf(fm, fabsf(fe[k]));
-        fm = fmaxf(fm, __shfl_xor(fm, 16, 64));
-        fm = fmaxf(fm, __shfl_xor(fm, 32, 64));
+        for (int k = 0; k < LY::NF; ++k) band += ga[k] * fabsf(fe[k]);
+        band += __shfl_xor(band, 16, 64);
+        band += __shfl_xor(band, 32, 64);
         const f4v raw = density_raw<NL, 4, 1, false>(sW, fe, lane);
-        const float band = kOccBand * fm * norm + 1e-6f * fabsf(F.density_offset);
+        band = 1.01f * band + 1e-6f * fabsf(F.density_offset);
         const float r = raw[0] + F.density_offset;   // lanes 0..15: raw output 0 of sample j
         yes |= softplusf(r - band) * 0.9999f >= thresh;
         maybe |= !(softplusf(r + band) * 1.0001f < thresh);
@@ -135,19 +143,39 @@ __global__ __launch_bounds__(256) void k_occupancy(FieldView F, const TabT* __re
       b = (b | (b >> 1)) & 0x3333u; b = (b | (b >> 2)) & 0x0F0Fu; b = (b | (b >> 4)) & 0xFFu;
       occ |= (uint64_t)a << (8 * run);
       open |= (uint64_t)(b & ~a) << (8 * run);
+      if (SHARED && lane == 0) s_run[run] = a | (b & ~a) << 8;
+    }
+    if constexpr (SHARED) {
+      __syncthreads();
+      occ = open = 0;
+      for (int k = 0; k < 8; ++k) {
+        occ |= (uint64_t)(s_run[k] & 0xFFu) << (8 * k);
+        open |= (uint64_t)(s_run[k] >> 8) << (8 * k);
+      }
+      __syncthreads();
+      if (wave != 0) continue;
+    }
+    while (open) {   // eight undecided cells at a time
+      int bit = 0;
+      uint64_t cells = 0;
+#pragma unroll 1
+      for (int k = 0; k < 8 && open; ++k) {
+        const int b = __builtin_ctzll(open);
+        open &= open - 1;
+        cells |= 1ull << b;
+        if (k <= lane >> 3) bit = b;
+      }
+      float px, py, pz;
+      probe_point(F, res, min(w * 64 + bit, n - 1), lane & 7, px, py, pz);
+      float best = probe_sigma<NL, TabT>(F, table, px, py, pz);
+#pragma unroll
+      for (int off = 1; off < 8; off <<= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+      const uint64_t yes = __ballot(best >= thresh);
+      for (int k = 0; cells; ++k, cells &= cells - 1)
+        if ((yes >> (8 * k)) & 1u) occ |= cells & (~cells + 1);
     }
     const int64_t c = w * 64 + lane;
-    bool o = c < n && ((occ >> lane) & 1u);
-    if (c < n && ((open >> lane) & 1u)) {
-      float best = -INFINITY;
-#pragma unroll 1
-      for (int s = 0; s < 8; ++s) {
-        float px, py, pz;
-        probe_point(F, res, c, s, px, py, pz);
-        best = fmaxf(best, probe_sigma<NL, TabT>(F, table, px, py, pz));
-      }
-      o = best >= thresh;
-    }
+    const bool o = c < n && ((occ >> lane) & 1u);
     if (bytes && c < n) bytes[c] = o ? 1 : 0;
     const uint64_t m = __ballot(o);
     if (lane == 0) words[2 * w] = (uint32_t)m;
@@ -158,9 +186,12 @@ __global__ __launch_bounds__(256) void k_occupancy(FieldView F, const TabT* __re
 template <int NL, typename TabT>
 mr_status launch_occ(mr_field* f, int res, float thresh, uint8_t* bytes, hipStream_t st) {
   const int64_t n = (int64_t)res * res * res;
-  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 2048);
-  hipLaunchKernelGGL((k_occupancy<NL, TabT>), dim3(blocks), dim3(256), 0, st, f->view,
-                     reinterpret_cast<const TabT*>(f->table_dev), f->frag_f32_dev, res, thresh, f->occ_dev, bytes);
+  const int64_t groups = (n + 63) / 64;
+  const bool shared = groups < 8 * (int64_t)device_cus();
+  auto* k = shared ? k_occupancy<NL, TabT, true> : k_occupancy<NL, TabT, false>;
+  const int blocks = (int)std::min<int64_t>(shared ? groups : (groups + 7) / 8, 2048);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(kOccThreads), 0, st, f->view, reinterpret_cast<const TabT*>(f->table_dev),
+                     f->frag_f32_dev, res, thresh, f->occ_dev, bytes);
   MR_HIP(hipGetLastError());
   return MR_OK;
 }
