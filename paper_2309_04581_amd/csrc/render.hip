@@ -160,8 +160,15 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace(RayQueue q, const int* __
 }
 
 // Queues of at most kTailRays rays have their closest hits traced by
-// k_trace_wide (one wave per ray) after the shade pass, not by it.
+// k_trace_wide (one wave per ray) after the shade pass, not by it, where the
+// mesh has more than kWideMinPrims triangles.
 constexpr int kTailRays = 2048;   // queues this short are traced a wave per ray
+// A small mesh's traversals are short on one thread too, and a launch per
+// segment costs more than they do: frames of n spheres at 64x64 / 256x256 with
+// and without k_trace_wide, 82 triangles: 403 / 781 and 225 / 682 us; 2 402:
+// 601 / 938 and 470 / 945; 8 002: 687 / 1123 and 667 / 1198; 20 002: 833 / 1437
+// and 926 / 1545.
+constexpr int kWideMinPrims = 4096;
 constexpr int kWideFront = 512;   // frontier nodes per wave and level
 constexpr int kWideWaves = 4;     // waves per block
 
@@ -187,7 +194,7 @@ template <bool MEDIUM>
 __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* __restrict__ count_in,
                                                        int* __restrict__ work, int tile, RayQueue qo,
                                                        int* __restrict__ count_out, MeshView M, ShadeParams S,
-                                                       RenderOut out, float span, int32_t* __restrict__ hit_ids,
+                                                       RenderOut out, float span, int tail, int32_t* __restrict__ hit_ids,
                                                        int hit_stride, unsigned long long* __restrict__ stats) {
   __shared__ int stack[kStack * kTraceBlock];
   __shared__ float tstack[kStack * kTraceBlock];
@@ -395,8 +402,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
       qo.rid[slot] = rid;
       qo.depth[slot] = ndepth;
       // closest hit of the new segment, whose range starts at the spawn point
-      // (for short queues k_trace_wide traces it, a wave per ray)
-      if (cnt > kTailRays) {
+      // (queues of at most `tail` rays are left to k_trace_wide, a wave per ray)
+      if (cnt > tail) {
         const RayPre nr = ray_pre(v3(nox, noy, noz), v3(ndx, ndy, ndz));
         float th = INFINITY;
         const int hp = bvh_trace<false>(M.bvh, nr, span, th, stack + threadIdx.x, tstack + threadIdx.x, kTraceBlock);
@@ -444,8 +451,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 __global__ __launch_bounds__(64 * kWideWaves) void k_trace_wide(RayQueue q, const int* __restrict__ gate_count,
-                                                               const int* __restrict__ count, int* __restrict__ work,
-                                                               BvhView B, float tmax, int32_t* __restrict__ hit_ids,
+                                                               const int* __restrict__ count, BvhView B, float tmax, int32_t* __restrict__ hit_ids,
                                                                int hit_stride) {
   __shared__ int s_node[kWideWaves][2][kWideFront];
   __shared__ float s_tin[kWideWaves][2][kWideFront];
@@ -455,11 +461,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_trace_wide(RayQueue q, cons
   const int cnt = *count;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long below = (1ull << lane) - 1ull;
-  while (true) {
-    int r = 0;
-    if (lane == 0) r = atomicAdd(work, 1);
-    r = __shfl(r, 0, 64);
-    if (r >= cnt) break;
+  // the queue is short: a wave has one ray, or a few, of its own
+  for (int r = blockIdx.x * kWideWaves + w; r < cnt; r += gridDim.x * kWideWaves) {
     const RayPre R = ray_pre(v3(q.ox[r], q.oy[r], q.oz[r]), v3(q.dx[r], q.dy[r], q.dz[r]));
     float tb = tmax;                     // best hit of the wave: (tb, idb) at triangle pb
     int pb = -1, idb = 0x7fffffff;
@@ -940,6 +943,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   const int shade_blocks =
       persistent_blocks(reinterpret_cast<const void*>(k_shade<false>), kTraceBlock, opts->stage_blocks_per_cu, tiles);
   const int packet_segments = opts->march_packets == 0 ? 1 : std::max(0, opts->march_packets);
+  const int tail = mv.bvh.n_prims > kWideMinPrims ? kTailRays : 0;
   const int wide_blocks = (int)std::max<int64_t>(
       1, std::min<int64_t>((std::min<int64_t>(n, kTailRays) + kWideWaves - 1) / kWideWaves, (int64_t)device_cus() * 4));
   for (int b = 0; b <= max_bounces; ++b) {
@@ -1002,7 +1006,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
       StageTimer tm(2, st, timed);
       auto* k = light_medium ? k_shade<true> : k_shade<false>;
       hipLaunchKernelGGL(k, dim3(shade_blocks), dim3(kTraceBlock), 0, st, qi, counts + b, swork + b, tile, qo,
-                         counts + b + 1, mv, S, ro, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
+                         counts + b + 1, mv, S, ro, P.span, tail, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
       MR_HIP(hipGetLastError());
       // no light sample on a ray's last segment
       for (int k = 0; light_medium && b < max_bounces && k < n_fields; ++k) {
@@ -1011,12 +1015,12 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
         if (s != MR_OK) return s;
       }
     }
-    if (b < max_bounces) {
+    if (b < max_bounces && tail > 0) {
       // closest hits of the next segment when this queue is short (the kernel
       // returns at once otherwise)
       StageTimer tm(0, st, timed);
       hipLaunchKernelGGL(k_trace_wide, dim3(wide_blocks), dim3(64 * kWideWaves), 0, st, qo, counts + b, counts + b + 1,
-                         twork + b + 1, mv.bvh, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0);
+                         mv.bvh, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0);
       MR_HIP(hipGetLastError());
     }
   }
