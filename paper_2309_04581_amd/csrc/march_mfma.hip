@@ -151,12 +151,13 @@ __device__ __forceinline__ PacketRay packet_ray(const RayQueue& q, int r, int cn
 
 // A packet of 16 rays stepped through the same sample index together:
 // column j of every tile is ray j at sample k, composited by a running
-// product per column.
-template <int NL, int SH, int CL, typename TabT, bool BF, bool SHADOW>
+// product per column.  SPLIT: the block's four waves take contiguous quarters
+// of the packet's steps, chained in order at the end as in march_ray_split.
+template <int NL, int SH, int CL, typename TabT, bool BF, bool SHADOW, bool SPLIT>
 __device__ __forceinline__ void march_packet(const RayQueue& q, const PacketRay& R, const FieldView& F,
                                              const TabT* __restrict__ table, const uint32_t* __restrict__ sW,
                                              const MarchParams& P, const BvhView& B, int* sstack, bool use_occ,
-                                             int lane, unsigned long long& nsamp) {
+                                             int lane, int wave, float (*part)[16][4], unsigned long long& nsamp) {
   using LY = FragLayout<NL, SH, CL, BF>;
   const int g = lane >> 4;
   const float delta = P.delta;
@@ -186,6 +187,11 @@ __device__ __forceinline__ void march_packet(const RayQueue& q, const PacketRay&
     kmax = max(kmax, __shfl_xor(kmax, off, 16));
   }
   if (kmin >= kmax) return;
+  if constexpr (SPLIT) {
+    const int per = (kmax - kmin + 3) / 4;
+    kmin += per * wave;
+    kmax = min(kmax, kmin + per);
+  }
   float u[4][4];
   sh_rows<NL, SH, CL, BF>(sW, dx, dy, dz, lane, u);
   float T = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
@@ -212,6 +218,23 @@ __device__ __forceinline__ void march_packet(const RayQueue& q, const PacketRay&
     T *= 1.0f - alpha;
     if (g == 0 && valid) ++nsamp;
   }
+  if constexpr (SPLIT) {
+    if (g == 0) *reinterpret_cast<float4*>(part[wave][lane]) = make_float4(T, acc0, acc1, acc2);
+    __syncthreads();
+    if (live && wave == 0 && g == 0) {
+      float T4 = 1.0f, l0 = 0.0f, l1 = 0.0f, l2 = 0.0f;
+      for (int w = 0; w < 4; ++w) {
+        const float4 p = *reinterpret_cast<const float4*>(part[w][lane]);
+        l0 += T4 * p.y;
+        l1 += T4 * p.z;
+        l2 += T4 * p.w;
+        T4 *= p.x;
+      }
+      ray_update(q, r, T4, l0, l1, l2);
+    }
+    __syncthreads();
+    return;
+  }
   if (live && g == 0) {
     const float tr = q.tr[r], tg = q.tg[r], tb = q.tb[r];
     q.lr[r] += tr * acc0;
@@ -229,6 +252,17 @@ __device__ __forceinline__ void march_packet(const RayQueue& q, const PacketRay&
 // At most this many rays per block: the per-ray march splits each ray over
 // the four waves of a block instead of taking one ray per wave.
 constexpr int kSplitRaysPerBlock = 8;
+// Up to this many packets per two blocks, each packet is split over a block's
+// four waves.  A packet walks its steps one after the other (1.4 us each on
+// the 8-level layout, 4 on the 16-level one), so with fewer packets than
+// waves a launch lasts as long as one packet: the camera march of a 64x64 tiny
+// frame took 87 us, 31 split.  One-bounce frames of 4 096 / 9 216 / 16 384 /
+// 36 864 rays, a packet per wave and split: 139 / 140 / 152 / 220 and 70 / 85 /
+// 109 / 155 us (8 levels); 4 096 / 9 216 / 16 384: 1 012 / 1 027 / 1 156 and
+// 592 / 862 / 1 187 us (16 levels, whose packets otherwise have producer and
+// consumer waves).
+template <int NL>
+constexpr int split_packets_per_two_blocks() { return NL == 16 ? 3 : 6; }
 
 template <int NL, int SH, int CL, typename TabT, bool BF, bool PK, bool SHADOW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_march_mfma(
@@ -264,11 +298,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
           march_ray<NL, SH, CL, TabT, BF, SHADOW>(q, r, F, table, sW, P, B, stack, use_occ, lane, nsamp);
         }
     }
+  } else if (cnt <= 8 * split_packets_per_two_blocks<NL>() * (int)gridDim.x) {
+    __shared__ __align__(16) float part[4][16][4];
+    for (int base = 16 * blockIdx.x; base < cnt; base += 16 * gridDim.x) {
+      const PacketRay R = packet_ray(q, base + j, cnt, F);
+      march_packet<NL, SH, CL, TabT, BF, SHADOW, true>(q, R, F, table, sW, P, B, stack, use_occ, lane,
+                                                       threadIdx.x >> 6, part, nsamp);
+    }
   } else {
     WorkQueue wq(work, cnt, P.chunk, 16);
     for (int base = wq.next(lane); base >= 0; base = wq.next(lane)) {
       const PacketRay R = packet_ray(q, wq.map(base + j), cnt, F);
-      march_packet<NL, SH, CL, TabT, BF, SHADOW>(q, R, F, table, sW, P, B, stack, use_occ, lane, nsamp);
+      march_packet<NL, SH, CL, TabT, BF, SHADOW, false>(q, R, F, table, sW, P, B, stack, use_occ, lane, 0, nullptr,
+                                                        nsamp);
     }
   }
   if (stats) {
@@ -522,22 +564,26 @@ mr_status launch_march_mode(const mr_field* f, RayQueue q, const int* count, int
                             const BvhView& B, unsigned long long* stats, int blocks_per_cu, int64_t n, hipStream_t st) {
   const uint32_t* fr = BF ? f->frag_bf16_dev : f->frag_f32_dev;
   const TabT* tab = reinterpret_cast<const TabT*>(f->table_dev);
+  auto* k = k_march_mfma<NL, SH, CL, TabT, BF, PK, SHADOW>;
+  const int64_t cap = PK ? (n + 15) / 16 : (n + 3) / 4;
+  const int blocks = persistent_blocks(reinterpret_cast<const void*>(k), 256, blocks_per_cu, cap);
   // producer and consumer waves pay for the 16-level layout; with 8 levels a
   // producer's gather is too short to hide behind a consumer's tile (the cloth
-  // workload ran 6.24 ms per frame with them against 5.56 ms without)
+  // workload ran 6.24 ms per frame with them against 5.56 ms without).  Few
+  // packets are split over a block's waves instead (above),
+  // unless the caller bounds the waits, which only the former have.
   if constexpr (PK && !SHADOW && NL == 16) {
-    auto* kp = k_march_pc<NL, SH, CL, TabT, BF>;
-    const int blocks = persistent_blocks(reinterpret_cast<const void*>(kp), kPcThreads, blocks_per_cu,
-                                         (n + 16 * kPcPairs - 1) / (16 * kPcPairs));
-    MarchParams Pw = P;
-    if (Pw.wait_polls <= 0) Pw.wait_polls = kPcSpin;
-    hipLaunchKernelGGL(kp, dim3(blocks), dim3(kPcThreads), 0, st, q, count, work, f->view, tab, fr, Pw, stats);
-    MR_HIP(hipGetLastError());
-    return MR_OK;
+    if (n > 8 * split_packets_per_two_blocks<NL>() * (int64_t)blocks || P.wait_polls > 0) {
+      auto* kp = k_march_pc<NL, SH, CL, TabT, BF>;
+      const int pairs = persistent_blocks(reinterpret_cast<const void*>(kp), kPcThreads, blocks_per_cu,
+                                          (n + 16 * kPcPairs - 1) / (16 * kPcPairs));
+      MarchParams Pw = P;
+      if (Pw.wait_polls <= 0) Pw.wait_polls = kPcSpin;
+      hipLaunchKernelGGL(kp, dim3(pairs), dim3(kPcThreads), 0, st, q, count, work, f->view, tab, fr, Pw, stats);
+      MR_HIP(hipGetLastError());
+      return MR_OK;
+    }
   }
-  auto* k = k_march_mfma<NL, SH, CL, TabT, BF, PK, SHADOW>;
-  const int64_t cap = PK ? (n + 63) / 64 : (n + 3) / 4;
-  const int blocks = persistent_blocks(reinterpret_cast<const void*>(k), 256, blocks_per_cu, cap);
   hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, count, work, f->view, tab, fr, P, B, stats);
   MR_HIP(hipGetLastError());
   return MR_OK;

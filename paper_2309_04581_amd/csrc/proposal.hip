@@ -266,6 +266,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // fine samples of the 16 rays are stepped together as with the plain packets
 // ---------------------------------------------------------------------------
 constexpr int kPkBins = 32;
+// A queue of at most this many rays is shorter one ray per wave: frames of
+// 4 096 / 9 216 / 16 384 rays took 443 / 600 / 719 us so and 545 / 620 / 658 in
+// packets (16 levels), 164 / 223 / 307 and 188 / 193 / 204 us (8 levels).
+constexpr int64_t kPkMinRays = 6144;
 
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -690,7 +694,7 @@ mr_status launch_prop_mode(const mr_field* f, const mr_field* p, RayQueue q, con
   const uint32_t* fr = BF ? f->frag_bf16_dev : f->frag_f32_dev;
   const TabT* tab = reinterpret_cast<const TabT*>(f->table_dev);
   const PTabT* ptab = reinterpret_cast<const PTabT*>(p->table_dev);
-  if (packets && n_prop == kPkBins && n_fine <= kPkBins) {
+  if (packets && n_prop == kPkBins && n_fine <= kPkBins && n > kPkMinRays) {
     auto* k = k_march_prop_pk<NL, SH, CL, TabT, BF, PTabT, SHADOW>;
     const int blocks = persistent_blocks(reinterpret_cast<const void*>(k), 256, blocks_per_cu, (n + 63) / 64);
     hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, count, work, f->view, tab, fr, p->view, ptab, P, B,

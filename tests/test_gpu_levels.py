@@ -3,6 +3,7 @@ per-ray march: a workspace of the ray queues alone turns the former off, and
 both must give the same bits."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2309_04581_amd import meshrf as M
 from paper_2309_04581_amd import scenegen as sg
@@ -19,7 +20,6 @@ def _render(F, G, o, d, sc, opts, lean):
     assert R.ws_bytes > _queues_bytes(len(o)), "no scratch for the level-by-level march"
     M.mr_render(F.handle, G.handle, len(o), o, d, sc.max_bounces, None, sc.lights, opts, R.out, R.workspace,
                 _queues_bytes(len(o)) if lean else R.ws_bytes)
-    import torch
     torch.cuda.synchronize()
     assert R.status() == 0
     return [t.cpu().numpy() for t in (R.radiance, R.throughput, R.bounces, R.hit_ids, R.counters)]
@@ -36,7 +36,6 @@ def _render(F, G, o, d, sc, opts, lean):
     (4096, False, True, False, -6.0),
 ])
 def test_levels_match_per_ray_march(n_samples, half, occ, posed, offset):
-    import torch
     sc = sg.mid_scene(width=331, height=257, n_samples=n_samples)   # 85 067 rays
     sc.max_bounces = 3
     f = sg.mid_field(9, 0.5, offset)
