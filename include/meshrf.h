@@ -118,7 +118,11 @@ mr_status mr_mlp_fragments(const mr_field_desc* desc, const float* host_mlp, int
 /* Evaluate the field at n points (device arrays).
  * x, dirs: (n, 3) in world coordinates (mapped into the field's frame when it
  * has a pose); sigma: (n); rgb: (n, 3) or NULL; feat: (n, n_levels*feats)
- * or NULL (interpolated hash features, FP32); raw: (n, density_out) or NULL. */
+ * or NULL (interpolated hash features, FP32); raw: (n, density_out) or NULL.
+ * Large queries of a 16-level field take 256 MiB of stream-ordered scratch
+ * (hipMallocFromPoolAsync) from a pool that keeps one such block per device
+ * until the last field is destroyed; under capture or without that memory
+ * they are evaluated without it, with the same results. */
 mr_status mr_field_query(const mr_field* f, int64_t n, const float* x, const float* dirs,
                          float* sigma, float* rgb, float* feat, float* raw, void* stream);
 

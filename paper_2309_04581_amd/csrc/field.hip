@@ -286,6 +286,7 @@ extern "C" mr_status mr_field_create(const mr_field_desc* desc, const float* hos
 
   hipStream_t st = (hipStream_t)stream;
   mr_field* f = new mr_field();
+  lv_fields(+1);
   f->desc = d;
   f->n_table = n_table;
   f->n_mlp = n_mlp;
@@ -392,6 +393,7 @@ extern "C" mr_status mr_field_destroy(mr_field* f) {
   if (f->frag_bf16_dev) (void)hipFree(f->frag_bf16_dev);
   if (f->master_dev) (void)hipFree(f->master_dev);
   if (f->opt_dev) (void)hipFree(f->opt_dev);
+  lv_fields(-1);
   delete f;
   return MR_OK;
 }

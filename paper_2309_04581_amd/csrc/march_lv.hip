@@ -1,95 +1,18 @@
-// March of incoherent segments (bounce rays) one hash level at a time.
-//
-// A bounce ray's samples share no line of the finer hashed levels, so the
-// per-ray march (march_mfma.hip) fetches about 49 lines per sample, 60 % of
-// them from beyond L2, and runs at the rate of random lines there (59 G/s).
-// One level of a 2^19-entry FP32 table is 4 MiB, what one die's L2 holds.
-// Here a block takes a batch of up to kLvSamples samples, evaluates level 0
-// of all of them, then level 1, ..., and keeps the features in a scratch area
-// of its own; the blocks of a die go from level to level together, so the
-// level's lines are fetched into each L2 once per batch of the whole die and
-// the gathers hit.  Then the block's waves run the MLP tiles ray by ray as the
-// per-ray march does: the same samples, arithmetic and order, the same bits.
-//
-// Two blocks share a compute unit and take turns: while one gathers, the
-// other runs its MLP tiles.  The turns and the levels are kept by counters
-// that only pace the blocks: every wait is bounded, and a block whose wait
-// runs out stops waiting.
-//
-// Encoding alone, 16 samples along each of many random rays: 0.62 ns per
-// sample per ray, 0.30 in these batches.  The bounce segments of the 800x800
-// mid frame (11.7 M samples) went from 7.4 to 5.4 ms in FP32, from 6.9 to
-// 4.7 ms with FP16 table and BF16 MLPs.
-#include "mr_march.h"
+// Kernels that evaluate incoherent samples one hash level at a time (mr_levels.h):
+// the march of bounce rays, and point queries.
+#include <mutex>
+
+#include "mr_field_kernels.h"
+#include "mr_levels.h"
 
 using namespace mr;
 
 namespace {
 
-constexpr int kLvThreads = 512;
-constexpr int kLvPer = kLvSamples / kLvThreads;   // samples per thread
-constexpr int kLvTiles = kLvSamples / 16;
-constexpr int kLvGrab = 64;                       // rays examined together (one wave)
-
-// Pacing of the blocks of one die and turn (blocks i and i + grid / 2 take
-// different turns).  Lines of their own: [die][turn] {levels, encodes done}.
-struct LvPace {
-  int *levels, *done, *other;
-  int per, phase, round, turn;
-  bool on;
-  __device__ __forceinline__ LvPace(int* base) {
-    const int half = gridDim.x / 2, die = blockIdx.x % kXcds;
-    turn = (int)blockIdx.x >= half ? 1 : 0;
-    per = half / kXcds;
-    levels = base + ((die * 2 + turn) * 2) * kLvLine;
-    done = levels + kLvLine;
-    other = base + ((die * 2 + (turn ^ 1)) * 2 + 1) * kLvLine;
-    phase = round = 0;
-    on = true;
-  }
-  __device__ __forceinline__ void wait(const int* c, int target, int polls) {
-    for (int i = 0; i < polls; ++i) {
-      if (__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) return;
-      __builtin_amdgcn_s_sleep(1);
-    }
-    on = false;
-  }
-  // one thread each; the callers hold the block's other threads at a barrier
-  __device__ __forceinline__ void my_turn() {
-    if (on) wait(other, per * (round + turn), 2048);
-    ++round;
-  }
-  __device__ __forceinline__ void next_level() {
-    ++phase;
-    __hip_atomic_fetch_add(levels, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (on) wait(levels, per * phase, 256);
-  }
-  __device__ __forceinline__ void skip(int n) {   // a batch without samples
-    phase += n;
-    __hip_atomic_fetch_add(levels, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __device__ __forceinline__ void encoded() {
-    __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __device__ __forceinline__ void leave() {   // nobody waits for this block again
-    __hip_atomic_fetch_add(levels, 1 << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_add(done, 1 << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-};
-
-// The blocks meet before every second hashed level (meeting before each one
-// costs more than it saves: 5.55 against 5.40 ms of bounce marches per mid
-// frame); the dense levels together are small.
-__device__ __forceinline__ bool paced(const FieldView& F, int l) {
-  return !((F.dense_mask >> l) & 1u) && ((l - __popc(F.dense_mask)) & 1) == 0;
-}
-
-struct LvRays {   // the batch's rays
-  float ox[kLvTiles], oy[kLvTiles], oz[kLvTiles], dx[kLvTiles], dy[kLvTiles], dz[kLvTiles];
-  float t_a[kLvTiles], lo[kLvTiles], hi[kLvTiles];
-  int r[kLvTiles], k0[kLvTiles], k1[kLvTiles], tile0[kLvTiles];
-};
-
+// March of bounce rays: the same samples, arithmetic and order as the per-ray
+// march (march_mfma.hip), the same bits.  The bounce segments of the 800x800
+// mid frame (11.7 M samples) went from 7.4 to 5.4 ms in FP32, from 6.9 to 4.7
+// ms with FP16 table and BF16 MLPs.
 template <int NL, int SH, int CL, typename TabT, bool BF>
 __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_march_lv(
     RayQueue q, const int* __restrict__ count, int* __restrict__ work, FieldView F, const TabT* __restrict__ table,
@@ -97,168 +20,43 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
     unsigned long long* __restrict__ stats) {
   using LY = FragLayout<NL, SH, CL, BF>;
   __shared__ __align__(16) uint32_t sW[LY::TOTAL];
-  __shared__ LvRays R;
-  __shared__ int sRayOf[kLvTiles];        // tile -> ray of the batch
-  __shared__ uint32_t sMask[kLvTiles];    // the tile's valid samples
-  __shared__ uint16_t sList[kLvSamples];  // valid samples of the batch, tile * 16 + column
-  __shared__ int sTiles, sRays, sValid, sNext;
+  __shared__ LvBatch B;
   const int cnt = *count;
   if (cnt < kLvMinRays) return;   // k_march_mfma takes a short queue
   for (int i = threadIdx.x; i < LY::TOTAL; i += kLvThreads) sW[i] = frags[i];
-  const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15, wave = threadIdx.x >> 6;
-  const bool use_occ = P.use_occupancy && F.occ;
+  const int lane = threadIdx.x & 63, j = lane & 15;
   const float delta = P.delta;
   double* my = scratch + (int64_t)blockIdx.x * kLvSamples * NL;
   LvPace pc(pace);
   unsigned long long nsamp = 0;
-  // rays per queue grab: several grabs per block, so that the blocks end together
-  const int grab = max(4, min(kLvGrab, cnt / (4 * (int)gridDim.x)));
-  int cur = 0, end = 0;   // wave 0: the rays grabbed and not yet batched
+  const int grab = lv_grab(cnt);
+  int cur = 0, end = 0;
   while (true) {
-    // --- the batch: wave 0 takes rays while their tiles fit ---
-    if (wave == 0) {
-      int tiles = 0, rays = 0;
-      while (tiles < kLvTiles) {
-        if (cur >= end) {
-          int v = 0;
-          if (lane == 0) v = atomicAdd(work, grab);
-          cur = __shfl(v, 0, 64);
-          end = min(cur + grab, cnt);
-          if (cur >= cnt) break;
-        }
-        const int r = cur + lane;
-        RaySeg S;
-        int nt = 0;
-        if (r < end && ray_seg(q, r, F, P, S)) nt = max(0, (S.k1 - S.k0 + 15) / 16);
-        int sum = nt;   // inclusive over the lanes
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const int u = __shfl_up(sum, off, 64);
-          if (lane >= off) sum += u;
-        }
-        const bool fits = tiles + sum <= kLvTiles && r < end;   // a prefix of the lanes (a ray has at most kLvTiles)
-        const uint64_t mf = __ballot(fits), ml = __ballot(fits && nt > 0);
-        if (fits && nt > 0) {
-          const int k = rays + __popcll(ml & ((1ull << lane) - 1ull)), t0 = tiles + sum - nt;
-          R.ox[k] = S.ox; R.oy[k] = S.oy; R.oz[k] = S.oz;
-          R.dx[k] = S.dx; R.dy[k] = S.dy; R.dz[k] = S.dz;
-          R.t_a[k] = S.t_a; R.lo[k] = S.lo; R.hi[k] = S.hi;
-          R.r[k] = r; R.k0[k] = S.k0; R.k1[k] = S.k1; R.tile0[k] = t0;
-          for (int t = 0; t < nt; ++t) sRayOf[t0 + t] = k;
-        }
-        const int nf = __popcll(mf);
-        if (nf > 0) tiles += __shfl(sum, nf - 1, 64);
-        rays += __popcll(ml);
-        cur += nf;
-        if (cur < end) break;   // the next ray does not fit: full
-      }
-      if (lane == 0) {
-        sTiles = tiles;
-        sRays = rays;
-        sValid = 0;
-        sNext = 0;
-      }
-    }
+    if (threadIdx.x < 64)
+      B.take(work, cnt, grab, cur, end, [&](int r, RaySeg& S) { return ray_seg(q, r, F, P, S); });
     __syncthreads();
-    const int tiles = sTiles, rays = sRays;
-    if (tiles == 0) break;
-    // --- the batch's valid samples ---
-    auto place = [&](int i, float& a, float& b, float& px, float& py, float& pz) {
-      const int t = i >> 4, k = sRayOf[t], s = R.k0[k] + 16 * (t - R.tile0[k]) + (i & 15);
-      const float ta = R.t_a[k];
-      a = fmaxf(ta + (float)s * delta, R.lo[k]);
-      b = fminf(ta + (float)(s + 1) * delta, R.hi[k]);
-      const float tm = 0.5f * (a + b);
-      px = R.ox[k] + tm * R.dx[k];
-      py = R.oy[k] + tm * R.dy[k];
-      pz = R.oz[k] + tm * R.dz[k];
-      return s < R.k1[k] && b > a;
-    };
-    for (int i0 = wave * 64; i0 < tiles * 16; i0 += kLvThreads) {
-      const int i = i0 + lane;
-      bool valid = i < tiles * 16;
-      float a, b, px, py, pz;
-      if (valid) valid = place(i, a, b, px, py, pz);
-      if (valid && use_occ) valid = occ_lookup(F, px, py, pz);
-      const uint64_t m = __ballot(valid);
-      if (j == 0 && i < tiles * 16) sMask[i >> 4] = (uint32_t)(m >> (lane & 48)) & 0xFFFFu;
-      int base = 0;
-      if (lane == 0 && m) base = atomicAdd(&sValid, __popcll(m));
-      base = __shfl(base, 0, 64);
-      if (valid) sList[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)i;
-    }
-    if (threadIdx.x == 0) pc.my_turn();
-    __syncthreads();
-    const int nv = sValid;
-    // --- the features, level by level ---
-    if (nv > 0) {
-      float xh[kLvPer], yh[kLvPer], zh[kLvPer];
-      int dst[kLvPer];
-#pragma unroll
-      for (int it = 0; it < kLvPer; ++it) {
-        const int e = it * kLvThreads + threadIdx.x, i = sList[min(e, nv - 1)];
-        float a, b, px, py, pz;
-        place(i, a, b, px, py, pz);
-        to_unit(F, px, py, pz, xh[it], yh[it], zh[it]);
-        dst[it] = e < nv ? (i >> 4) * NL * 16 + (i & 15) : -1;
-      }
-#pragma unroll 1
-      for (int l = 0; l < NL; ++l) {
-        if (paced(F, l)) {
-          __syncthreads();
-          if (threadIdx.x == 0) pc.next_level();
-          __syncthreads();
-        }
-#pragma unroll
-        for (int it = 0; it < kLvPer; ++it)
-          if (it * kLvThreads + wave * 64 < nv) {
-            const float2 f = encode_level_pair<TabT>(F, table, l, lane, xh[it], yh[it], zh[it]);
-            if (dst[it] >= 0) __builtin_nontemporal_store(__builtin_bit_cast(double, f), my + dst[it] + l * 16);
-          }
-      }
-    } else if (threadIdx.x == 0) {
-      int waits = 0;
-      for (int l = 0; l < NL; ++l) waits += paced(F, l);
-      pc.skip(waits);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) pc.encoded();
-    // --- MLP tiles and compositing, a ray per wave ---
-    while (true) {
-      int k = 0;
-      if (lane == 0) k = atomicAdd(&sNext, 1);
-      k = __shfl(k, 0, 64);
-      if (k >= rays) break;
-      const int t0 = R.tile0[k], nt = (R.k1[k] - R.k0[k] + 15) / 16;
-      const float t_a = R.t_a[k], lo = R.lo[k], hi = R.hi[k];
+    if (B.n_tiles == 0) break;
+    B.encode<NL, TabT>(F, table, pc, delta, P.use_occupancy && F.occ, my);
+    // MLP tiles and compositing, a ray per wave
+    for (int k = B.next_ray(); k >= 0; k = B.next_ray()) {
+      const int t0 = B.tile0[k], nt = (B.k1[k] - B.k0[k] + 15) / 16;
+      const float t_a = B.t_a[k], lo = B.lo[k], hi = B.hi[k];
       // the ray's throughput (lanes 0..2) and radiance (3..5), needed at its end
-      float* state = q.tr + (int64_t)min(lane, 5) * (q.tg - q.tr) + R.r[k];
+      float* state = q.tr + (int64_t)min(lane, 5) * (q.tg - q.tr) + B.r[k];
       const float old = *state;
       float u[4][4];
-      sh_rows<NL, SH, CL, BF>(sW, R.dx[k], R.dy[k], R.dz[k], lane, u);
+      sh_rows<NL, SH, CL, BF>(sW, B.dx[k], B.dy[k], B.dz[k], lane, u);
       float Tseg = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
-      double nx[NL / 4];
-#pragma unroll
-      for (int ll = 0; ll < NL / 4; ++ll) nx[ll] = __builtin_nontemporal_load(my + ((int64_t)t0 * NL + 4 * ll + g) * 16 + j);
+      d4v ahead = lv_load(my, t0, lane);
       for (int t = 0; t < nt; ++t) {
-        const uint32_t m = sMask[t0 + t];
-        double cu[NL / 4];
-#pragma unroll
-        for (int ll = 0; ll < NL / 4; ++ll) {
-          cu[ll] = nx[ll];
-          nx[ll] = __builtin_nontemporal_load(my + ((int64_t)min(t0 + t + 1, kLvTiles - 1) * NL + 4 * ll + g) * 16 + j);
-        }
-        if (m == 0) continue;
-        const int s = R.k0[k] + 16 * t + j;
+        const uint32_t m = B.mask[t0 + t];
         const bool valid = (m >> j) & 1u;
-        const float D = fminf(t_a + (float)(s + 1) * delta, hi) - fmaxf(t_a + (float)s * delta, lo);
         float fe[LY::NF];
-#pragma unroll
-        for (int ll = 0; ll < NL / 4; ++ll) {
-          const float2 f = __builtin_bit_cast(float2, cu[ll]);
-          fe[2 * ll] = valid ? f.x : 0.0f;
-          fe[2 * ll + 1] = valid ? f.y : 0.0f;
-        }
+        lv_features(ahead, valid, fe);
+        ahead = lv_load(my, t0 + t + 1, lane);
+        if (m == 0) continue;
+        const int s = B.k0[k] + 16 * t + j;
+        const float D = fminf(t_a + (float)(s + 1) * delta, hi) - fmaxf(t_a + (float)s * delta, lo);
         float sigma, rgb[3];
         f4v raw;
         mlp_tile<NL, SH, CL, BF>(sW, fe, u, F.density_offset, lane, sigma, rgb, raw);
@@ -286,15 +84,111 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
   if (stats && lane == 0 && nsamp) atomicAdd(stats + 0, nsamp);
 }
 
+// Point queries (3 M random points of a 16-level field, all outputs but features
+// and raw: 2.67 ms in k_query_mfma, 1.29 here; FP16 and BF16 2.13 and 1.04).  A
+// block takes `batch` consecutive points at a time (a multiple of 64, at most
+// kLvSamples, chosen so that the blocks have equal numbers of batches).
+template <int NL, int SH, int CL, typename TabT, bool BF>
+__global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_query_lv(
+    FieldView F, const TabT* __restrict__ table, const uint32_t* __restrict__ frags, int64_t n, int batch,
+    const float* __restrict__ x, const float* __restrict__ dirs, float* __restrict__ sigma_out,
+    float* __restrict__ rgb_out, float* __restrict__ feat_out, float* __restrict__ raw_out,
+    double* __restrict__ scratch, int* __restrict__ pace) {
+  using LY = FragLayout<NL, SH, CL, BF>;
+  __shared__ __align__(16) uint32_t sW[LY::TOTAL];
+  for (int i = threadIdx.x; i < LY::TOTAL; i += kLvThreads) sW[i] = frags[i];
+  const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15, wave = threadIdx.x >> 6;
+  double* my = scratch + (int64_t)blockIdx.x * kLvSamples * NL;
+  LvPace pc(pace);
+  for (int64_t base = (int64_t)blockIdx.x * batch; base < n; base += (int64_t)gridDim.x * batch) {
+    const int nv = (int)min((int64_t)batch, n - base);
+    float xh[kLvPer], yh[kLvPer], zh[kLvPer];
+    int dst[kLvPer];
+#pragma unroll
+    for (int it = 0; it < kLvPer; ++it) {
+      const int e = it * kLvThreads + threadIdx.x;
+      const int64_t p = base + min(e, nv - 1);
+      float px = x[3 * p], py = x[3 * p + 1], pz = x[3 * p + 2], dx = 0.0f, dy = 0.0f, dz = 0.0f;
+      to_field_frame(F, px, py, pz, dx, dy, dz);
+      to_unit(F, px, py, pz, xh[it], yh[it], zh[it]);
+      dst[it] = e < nv ? (e >> 4) * NL * 16 + (e & 15) : -1;
+    }
+    if (threadIdx.x == 0) pc.my_turn();
+    __syncthreads();
+    lv_levels<NL, TabT>(F, table, pc, nv, xh, yh, zh, dst, my);
+    __syncthreads();
+    if (threadIdx.x == 0) pc.encoded();
+    d4v ahead = lv_load(my, wave, lane);
+    for (int t = wave; t * 16 < nv; t += kLvThreads / 64) {
+      const bool valid = t * 16 + j < nv;
+      float fe[LY::NF];
+      lv_features(ahead, valid, fe);
+      ahead = lv_load(my, t + kLvThreads / 64, lane);
+      const int64_t p = base + t * 16 + j, pc2 = valid ? p : n - 1;
+      float px = 0.0f, py = 0.0f, pz = 0.0f, dx = 0.0f, dy = 0.0f, dz = 1.0f;
+      if (dirs) { dx = dirs[3 * pc2]; dy = dirs[3 * pc2 + 1]; dz = dirs[3 * pc2 + 2]; }
+      to_field_frame(F, px, py, pz, dx, dy, dz);
+      float u[4][4];
+      sh_rows<NL, SH, CL, BF>(sW, dx, dy, dz, lane, u);
+      float sigma, rgb[3];
+      f4v raw;
+      mlp_tile<NL, SH, CL, BF>(sW, fe, u, F.density_offset, lane, sigma, rgb, raw);
+      if (!valid) continue;
+      if (g == 0) {
+        sigma_out[p] = sigma;
+        if (rgb_out) {
+          rgb_out[3 * p] = rgb[0];
+          rgb_out[3 * p + 1] = rgb[1];
+          rgb_out[3 * p + 2] = rgb[2];
+        }
+      }
+      if (feat_out)
+#pragma unroll
+        for (int k = 0; k < LY::NF; ++k) feat_out[p * 2 * NL + frag_k(0, LY::NF, 0, g, k)] = fe[k];
+      if (raw_out)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) raw_out[p * 16 + 4 * g + v] = raw[v];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) pc.leave();
+}
+
+__global__ void k_zero_pace(int* __restrict__ p) {
+  for (int i = threadIdx.x; i < kLvPaceInts; i += blockDim.x) p[i] = 0;
+}
+
 template <int SH, int CL, typename TabT, bool BF>
-mr_status launch_lv(const mr_field* f, RayQueue q, const int* count, int* work, const MarchParams& P, const LvScratch& lv,
-                    unsigned long long* stats, hipStream_t st) {
+mr_status launch_lv(const mr_field* f, RayQueue q, const int* count, int* work, const MarchParams& P,
+                    const LvScratch& lv, unsigned long long* stats, hipStream_t st) {
   hipLaunchKernelGGL((k_march_lv<16, SH, CL, TabT, BF>), dim3(lv_blocks()), dim3(kLvThreads), 0, st, q, count, work,
                      f->view, reinterpret_cast<const TabT*>(f->table_dev), BF ? f->frag_bf16_dev : f->frag_f32_dev, P,
                      lv.feat, lv.pace, stats);
   MR_HIP(hipGetLastError());
   return MR_OK;
 }
+
+template <int SH, int CL, typename TabT, bool BF>
+mr_status launch_query_lv(const mr_field* f, int64_t n, const float* x, const float* dirs, float* sigma, float* rgb,
+                          float* feat, float* raw, const LvScratch& lv, hipStream_t st) {
+  const int64_t grid = lv_blocks(), rounds = (n + grid * kLvSamples - 1) / (grid * kLvSamples);
+  const int batch = (int)((n + grid * rounds * 64 - 1) / (grid * rounds * 64)) * 64;
+  hipLaunchKernelGGL((k_query_lv<16, SH, CL, TabT, BF>), dim3((unsigned)grid), dim3(kLvThreads), 0, st, f->view,
+                     reinterpret_cast<const TabT*>(f->table_dev), BF ? f->frag_bf16_dev : f->frag_f32_dev, n, batch, x,
+                     dirs, sigma, rgb, feat, raw, lv.feat, lv.pace);
+  MR_HIP(hipGetLastError());
+  return MR_OK;
+}
+
+// Scratch of calls without a workspace: stream-ordered blocks of a memory pool
+// per device, so calls on several streams and threads each have their own and
+// a returned block is taken again in stream order.  The pool keeps at most one
+// block beyond the calls (its release threshold) and is trimmed when the last
+// field is destroyed.
+constexpr int kMaxDevices = 64;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kMaxDevices] = {};
+int g_fields = 0;
 
 }  // namespace
 
@@ -310,21 +204,75 @@ bool lv_field(const mr_field* f) {
   return v.n_levels == 16 && level <= (8u << 20) && level * 16 > (4u << 20);
 }
 
+bool lv_lease(hipStream_t st, LvScratch* lv) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = 0;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+      hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
+    (void)hipGetLastError();
+    return false;
+  }
+  hipMemPool_t pool = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (!g_pool[dev]) {
+      hipMemPoolProps props = {};
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = dev;
+      uint64_t keep = lv_bytes();
+      if (hipMemPoolCreate(&g_pool[dev], &props) != hipSuccess ||
+          hipMemPoolSetAttribute(g_pool[dev], hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+      }
+    }
+    pool = g_pool[dev];
+  }
+  void* p = nullptr;
+  if (hipMallocFromPoolAsync(&p, lv_bytes(), pool, st) != hipSuccess || !p) {
+    (void)hipGetLastError();
+    return false;
+  }
+  lv->pace = reinterpret_cast<int*>(p);
+  lv->feat = reinterpret_cast<double*>(reinterpret_cast<char*>(p) + kLvPaceArea);
+  hipLaunchKernelGGL(k_zero_pace, dim3(1), dim3(kLvPaceInts), 0, st, lv->pace);
+  return true;
+}
+
+void lv_return(hipStream_t st, const LvScratch& lv) { (void)hipFreeAsync(lv.pace, st); }
+
+void lv_fields(int change) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  g_fields += change;
+  if (g_fields > 0) return;
+  for (hipMemPool_t p : g_pool)
+    if (p) (void)hipMemPoolTrimTo(p, 0);
+}
+
+#define LV_DISPATCH(fn, ...)                                       \
+  do {                                                             \
+    const auto& v = f->view;                                       \
+    const bool h = v.table_dtype == MR_F16, bf = v.mlp_dtype == MR_BF16; \
+    if (v.sh == 16 && v.c_layers == 2) {                           \
+      if (bf) return h ? fn<16, 2, __half, true>(__VA_ARGS__) : fn<16, 2, float, true>(__VA_ARGS__);   \
+      return h ? fn<16, 2, __half, false>(__VA_ARGS__) : fn<16, 2, float, false>(__VA_ARGS__);         \
+    }                                                              \
+    if (v.sh == 4 && v.c_layers == 1) {                            \
+      if (bf) return h ? fn<4, 1, __half, true>(__VA_ARGS__) : fn<4, 1, float, true>(__VA_ARGS__);     \
+      return h ? fn<4, 1, __half, false>(__VA_ARGS__) : fn<4, 1, float, false>(__VA_ARGS__);           \
+    }                                                              \
+    return fail(MR_ERR_UNSUPPORTED, "field shape not instantiated"); \
+  } while (0)
+
 mr_status dispatch_march_lv(const mr_field* f, RayQueue q, const int* count, int* work, const MarchParams& P,
                             const LvScratch& lv, unsigned long long* stats, hipStream_t st) {
-  const auto& v = f->view;
-  const bool h = v.table_dtype == MR_F16, bf = v.mlp_dtype == MR_BF16;
-#define L(SH, CL)                                                                                    \
-  if (v.sh == SH && v.c_layers == CL) {                                                              \
-    if (bf) return h ? launch_lv<SH, CL, __half, true>(f, q, count, work, P, lv, stats, st)     \
-                     : launch_lv<SH, CL, float, true>(f, q, count, work, P, lv, stats, st);     \
-    return h ? launch_lv<SH, CL, __half, false>(f, q, count, work, P, lv, stats, st)            \
-             : launch_lv<SH, CL, float, false>(f, q, count, work, P, lv, stats, st);            \
-  }
-  L(16, 2)
-  L(4, 1)
-#undef L
-  return fail(MR_ERR_UNSUPPORTED, "field shape not instantiated");
+  LV_DISPATCH(launch_lv, f, q, count, work, P, lv, stats, st);
+}
+
+mr_status query_lv(const mr_field* f, int64_t n, const float* x, const float* dirs, float* sigma, float* rgb,
+                   float* feat, float* raw, const LvScratch& lv, hipStream_t st) {
+  LV_DISPATCH(launch_query_lv, f, n, x, dirs, sigma, rgb, feat, raw, lv, st);
 }
 
 }  // namespace mr

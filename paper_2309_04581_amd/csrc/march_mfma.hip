@@ -716,6 +716,12 @@ mr_status dispatch_march_mfma(const mr_field* f, RayQueue q, const int* count, i
 mr_status query_mfma(const mr_field* f, int64_t n, const float* x, const float* dirs, float* sigma, float* rgb,
                      float* feat, float* raw, hipStream_t st) {
   const auto& v = f->view;
+  LvScratch lv;
+  if (n >= lv_min_points(f) && lv_field(f) && lv_lease(st, &lv)) {
+    const mr_status s = query_lv(f, n, x, dirs, sigma, rgb, feat, raw, lv, st);
+    lv_return(st, lv);
+    return s;
+  }
   const bool h = v.table_dtype == MR_F16, bf = v.mlp_dtype == MR_BF16;
 #define Q(NL, SH, CL)                                                                                          \
   if (v.n_levels == NL && v.sh == SH && v.c_layers == CL) {                                                     \

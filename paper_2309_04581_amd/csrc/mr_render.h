@@ -185,7 +185,21 @@ struct LvScratch {
 };
 int lv_blocks();
 size_t lv_bytes();
-bool lv_field(const mr_field* f);
+// Point queries go level by level from this many points: 50 000 / 100 000 / 1 M
+// random points took 107 / 193 / 1 053 us in k_query_mfma and 99 / 128 / 512
+// level by level (FP32), 68 / 121 / 767 and 88 / 109 / 385 (FP16 table, whose
+// levels are half as large).
+inline int64_t lv_min_points(const mr_field* f) { return f->view.table_dtype == MR_F16 ? 98304 : 49152; }
+bool lv_field(const mr_field* f);   // a field whose levels fit a die's L2 and whose table does not
+
+// Scratch for a call without a workspace (false under capture or without
+// memory: the caller then takes the general path), and its return after the
+// call's launches.  lv_fields counts the live fields (+1, -1).
+bool lv_lease(hipStream_t st, LvScratch* lv);
+void lv_return(hipStream_t st, const LvScratch& lv);
+void lv_fields(int change);
+mr_status query_lv(const mr_field* f, int64_t n, const float* x, const float* dirs, float* sigma, float* rgb,
+                   float* feat, float* raw, const LvScratch& lv, hipStream_t st);
 mr_status dispatch_march_lv(const mr_field* f, RayQueue q, const int* count, int* work, const MarchParams& P,
                             const LvScratch& lv, unsigned long long* stats, hipStream_t st);
 

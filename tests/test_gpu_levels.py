@@ -68,3 +68,55 @@ def test_levels_of_other_table_sizes(log2_table, n_levels):
     b = _render(F, G, o, d, sc, opts, lean=True)
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
+
+
+def _query(F, x, d, **kw):
+    r = F.query(x, d, **kw)
+    return {k: v for k, v in r.items() if v is not None}
+
+
+# just below and above the change of path, ragged ends, one and two batches per block
+@pytest.mark.parametrize("half,n,posed", [(False, 49151, False), (False, 49153, True), (True, 98305, False),
+                                          (False, 200001, False), (True, 131072 + 17, True), (False, 2200003, False)])
+def test_large_query_matches_small_ones(half, n, posed):
+    f = sg.mid_field(4, 1.0)
+    if posed:
+        f.pose = sg.pose_matrix(sg.rotation((0.3, 1.0, 0.2), 0.4), (0.1, -0.05, 0.15))
+    F = M.Field(f, **(dict(table_dtype=M.MR_F16, mlp_dtype=M.MR_BF16) if half else {}))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.rand(n, 3, device="cuda", generator=g) * 2.2 - 1.1
+    d = torch.nn.functional.normalize(torch.randn(n, 3, device="cuda", generator=g), dim=1)
+    want = dict(want_feat=n < 10 ** 6, want_raw=n < 10 ** 6)
+    a = _query(F, x, d, **want)
+    parts = [_query(F, x[i:i + 40000].contiguous(), d[i:i + 40000].contiguous(), **want) for i in range(0, n, 40000)]
+    for k in a:
+        assert torch.equal(a[k], torch.cat([p[k] for p in parts])), k
+    s = _query(F, x, None, want_rgb=False)
+    assert torch.equal(s["sigma"], a["sigma"])
+
+
+def test_large_query_on_two_streams_and_under_capture():
+    F = M.Field(sg.mid_field(4, 1.0))
+    n = 150000
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = [torch.rand(n, 3, device="cuda", generator=g) * 2 - 1 for _ in range(2)]
+    ref = [F.query(p, None, want_rgb=False)["sigma"].clone() for p in x]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    got = [[], []]
+    for _ in range(4):
+        for k, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got[k].append(F.query(x[k], None, want_rgb=False)["sigma"])
+    torch.cuda.synchronize()
+    for k in range(2):
+        for v in got[k]:
+            assert torch.equal(v, ref[k])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = F.query(x[0], None, want_rgb=False)["sigma"]
+    for k in (0, 1, 0):
+        x[0].copy_(x[k].clone())
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, F.query(x[0], None, want_rgb=False)["sigma"])
