@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
 }
 
 __global__ void k_zero_pace(int* __restrict__ p) {
-  for (int i = threadIdx.x; i < kLvPaceInts; i += blockDim.x) p[i] = 0;
+  for (int i = threadIdx.x; i <= kLvPaceInts; i += blockDim.x) p[i] = 0;
 }
 
 template <int SH, int CL, typename TabT, bool BF>

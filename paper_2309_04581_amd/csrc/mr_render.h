@@ -93,8 +93,8 @@ constexpr int kXcds = 8;               // accelerator complex dies; workgroups g
 
 // Counters in the workspace header: live rays, closest-hit and shade queue
 // heads and kXcds march queue heads per segment, the march waits that gave up,
-// and a light-sample queue head per segment.
-constexpr int kHeaderCounters = (4 + kXcds) * (kMaxBounces + 2) + 1;
+// and two light-sample queue heads per segment.
+constexpr int kHeaderCounters = (5 + kXcds) * (kMaxBounces + 2) + 1;
 
 // Ray work queue of the persistent march kernels.  chunk == 0: one queue for
 // the whole device.  chunk > 0: the rays [0, cnt) are cut into chunks of
@@ -154,18 +154,6 @@ mr_status dispatch_march_fields(const mr_field* const* fields, int n_fields, Ray
                                 const MarchParams& P, const BvhView& B, bool packets, unsigned long long* stats,
                                 int blocks_per_cu, int64_t n, hipStream_t st);
 
-// Medium of the light samples toward emitters (light_march.hip).  The shade
-// pass leaves a light sample's record in the slot of the ray it shaded, in the
-// queue it has read: origin and direction of the shadow segment, its length in
-// hit_t, the light it carries in tr tg tb, the optical depth so far (0) in lr,
-// where the light goes in rid (s >= 0: the ray in slot s of the next queue,
-// ~i: the finished caller's ray i) and kLightPending in hit_p.  One launch per
-// field adds that field's depth; the last one adds the light times the
-// transmittance to the ray.  work: a zeroed counter, or null for a fixed split.
-constexpr int kLightPending = 1;
-mr_status dispatch_light_march(const mr_field* f, RayQueue q, RayQueue next, const int* count, int* work, float delta,
-                               bool use_occupancy, bool last, float* radiance, int64_t n, hipStream_t st);
-
 // march of incoherent segments level by level (march_lv.hip); it leaves queues
 // of fewer than kLvMinRays rays alone.  Its scratch in the workspace: kLvPaceArea
 // bytes of pacing counters, kLvPaceInts for each launch and zeroed with the
@@ -178,7 +166,7 @@ constexpr int kLvMinRays = 8192;
 constexpr int64_t kLvMinFrame = 65536;
 constexpr int kLvLine = 32;        // words between two counters: a 128-byte line each
 constexpr int kLvPaceInts = kXcds * 4 * kLvLine;
-constexpr size_t kLvPaceArea = (size_t)(kMaxBounces + 2) * kLvPaceInts * sizeof(int);
+constexpr size_t kLvPaceArea = 2 * (size_t)(kMaxBounces + 2) * kLvPaceInts * sizeof(int);
 struct LvScratch {
   int* pace;      // this launch's counters
   double* feat;   // (feature 0, feature 1) pairs
@@ -194,7 +182,8 @@ bool lv_field(const mr_field* f);   // a field whose levels fit a die's L2 and w
 
 // Scratch for a call without a workspace (false under capture or without
 // memory: the caller then takes the general path), and its return after the
-// call's launches.  lv_fields counts the live fields (+1, -1).
+// call's launches.  The counters of one launch are zeroed, and so is the word
+// after them (a queue head).  lv_fields counts the live fields (+1, -1).
 bool lv_lease(hipStream_t st, LvScratch* lv);
 void lv_return(hipStream_t st, const LvScratch& lv);
 void lv_fields(int change);
@@ -202,6 +191,21 @@ mr_status query_lv(const mr_field* f, int64_t n, const float* x, const float* di
                    float* feat, float* raw, const LvScratch& lv, hipStream_t st);
 mr_status dispatch_march_lv(const mr_field* f, RayQueue q, const int* count, int* work, const MarchParams& P,
                             const LvScratch& lv, unsigned long long* stats, hipStream_t st);
+
+// Medium of the light samples toward emitters (light_march.hip).  The shade
+// pass leaves a light sample's record in the slot of the ray it shaded, in the
+// queue it has read: origin and direction of the shadow segment, its length in
+// hit_t, the light it carries in tr tg tb, the optical depth so far (0) in lr,
+// where the light goes in rid (s >= 0: the ray in slot s of the next queue,
+// ~i: the finished caller's ray i) and kLightPending in hit_p.  One launch per
+// field adds that field's depth; the last one adds the light times the
+// transmittance to the ray.  work: a zeroed counter for each of two kernels,
+// kMaxBounces + 2 apart, or null for a fixed split; lv: scratch for marching a
+// long queue level by level (one field that lv_field accepts), or null.
+constexpr int kLightPending = 1;
+mr_status dispatch_light_march(const mr_field* f, RayQueue q, RayQueue next, const int* count, int* work, float delta,
+                               bool use_occupancy, bool last, float* radiance, int64_t n, const LvScratch* lv,
+                               hipStream_t st);
 
 // proposal-sampled march (defined with the proposal kernels)
 // packets: 16 consecutive queue rays per wave when n_prop = 32 and n_fine <= 32

@@ -862,7 +862,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   int* swork = twork + (kMaxBounces + 2);                   // shade tile queue heads
   int* work = swork + (kMaxBounces + 2);                    // march: kXcds ray queue heads per segment
   int* gave_up = work + kXcds * (kMaxBounces + 2);          // march waits that gave up (mr_render_status)
-  int* lwork = gave_up + 1;                                 // light-sample march: a queue head per segment
+  int* lwork = gave_up + 1;                                 // light-sample march: two queue heads per segment
   RayQueue Q[2] = {queue_at(ws + kHeaderBytes, cap), queue_at(ws + kHeaderBytes + queue_bytes(cap), cap)};
   int* fctr = reinterpret_cast<int*>(ws + queues_bytes(n, 1));     // several fields only
   float* fscratch = reinterpret_cast<float*>(ws + queues_bytes(n, 1) + kFieldCtrBytes);
@@ -905,12 +905,14 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   // workspace has the scratch area for it
   int* lv_pace = reinterpret_cast<int*>(ws + queues_bytes(n, n_fields));
   double* lv_feat = reinterpret_cast<double*>(reinterpret_cast<char*>(lv_pace) + kLvPaceArea);
-  P.lv = n_fields == 1 && opts->sampler == MR_SAMPLER_UNIFORM && !P.shadows && n >= kLvMinFrame &&
-         workspace_bytes >= queues_bytes(n, n_fields) + lv_bytes() && lv_field(field);
+  const bool lv = n_fields == 1 && n >= kLvMinFrame && workspace_bytes >= queues_bytes(n, n_fields) + lv_bytes() &&
+                  lv_field(field);
+  const bool lv_light = lv && opts->sample_emitters;
+  P.lv = lv && opts->sampler == MR_SAMPLER_UNIFORM && !P.shadows;
 
   const int init_blocks = (int)std::min<int64_t>((n + 255) / 256, 65535);
   hipLaunchKernelGGL(k_init, dim3(init_blocks), dim3(256), 0, st, n, origins, dirs, per_ray_max_bounces, max_bounces,
-                     Q[0], counts, kHeaderCounters, lv_pace, P.lv ? (max_bounces + 1) * kLvPaceInts : 0,
+                     Q[0], counts, kHeaderCounters, lv_pace, lv ? 2 * (max_bounces + 1) * kLvPaceInts : 0,
                      out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
   MR_HIP(hipGetLastError());
 
@@ -1009,9 +1011,11 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
                          counts + b + 1, mv, S, ro, P.span, tail, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
       MR_HIP(hipGetLastError());
       // no light sample on a ray's last segment
+      const LvScratch light_lv = {lv_pace + kLvPaceInts * (max_bounces + 1 + b), lv_feat};
       for (int k = 0; light_medium && b < max_bounces && k < n_fields; ++k) {
         s = dispatch_light_march(fields[k], qi, qo, counts + b, k == 0 ? lwork + b : nullptr, light_delta,
-                                 opts->use_occupancy != 0, k + 1 == n_fields, ro.radiance, n, st);
+                                 opts->use_occupancy != 0, k + 1 == n_fields, ro.radiance, n, lv_light ? &light_lv : nullptr,
+                                 st);
         if (s != MR_OK) return s;
       }
     }

@@ -120,3 +120,22 @@ def test_large_query_on_two_streams_and_under_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, F.query(x[0], None, want_rgb=False)["sigma"])
+
+
+# 4096: light segments of more intervals than a batch holds go to the general
+# kernel (spacing 0.95 / 4096, segments of up to about 2)
+@pytest.mark.parametrize("depth_samples,half,occ", [(0, False, True), (32, True, False), (4096, False, False)])
+def test_light_samples_level_by_level(depth_samples, half, occ):
+    sc = sg.emitter_scene(width=331, height=257)
+    sc.max_bounces, sc.n_samples = 2, 64
+    sc.t_far = 4.0 if depth_samples != 4096 else 1.0
+    F = M.Field(sg.mid_field(9, 0.5, -1.0), **(dict(table_dtype=M.MR_F16, mlp_dtype=M.MR_BF16) if half else {}))
+    if occ:
+        F.build_occupancy(64, 0.3)
+    G = M.Mesh(sc.mesh)
+    o, d, _ = M.camera_rays(sg.cameras_array(sc.cameras))
+    opts = M.make_opts(sc, use_occupancy=occ, sample_emitters=True, light_depth_samples=depth_samples)
+    a = _render(F, G, o, d, sc, opts, lean=False)
+    b = _render(F, G, o, d, sc, opts, lean=True)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
