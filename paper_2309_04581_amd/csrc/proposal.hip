@@ -17,8 +17,7 @@
 #include <vector>
 
 #include "mr_field_kernels.h"
-#include "mr_mfma.h"
-#include "mr_render.h"
+#include "mr_levels.h"
 
 using namespace mr;
 
@@ -449,6 +448,104 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(prop_pk_wav
 // training targets: the plain marcher's weights of the camera segment,
 // histogrammed over n_bins equal bins of [lo, hi] by interval overlap
 // ---------------------------------------------------------------------------
+// What the 16 samples of a tile (interval [a, b] of length D, weight w) add to
+// the histogram: lane l returns bin l's share.
+__device__ __forceinline__ float tile_bins(float a, float b, float D, float w, bool valid, float lo, float bw,
+                                           int n_bins, int lane) {
+  float hist = 0.0f;
+  const float ta = __shfl(a, 0, 64), tb = __shfl(b, 15, 64);
+  const int bmin = max(0, (int)floorf((ta - lo) / bw) - 1);
+  const int bmax = min(n_bins - 1, (int)floorf((tb - lo) / bw) + 1);
+  for (int bb = bmin; bb <= bmax; ++bb) {
+    const float c0 = lo + (float)bb * bw, c1 = lo + (float)(bb + 1) * bw;
+    const float ov = fminf(b, c1) - fmaxf(a, c0);
+    const float part = (valid && ov > 0.0f) ? w * ov / D : 0.0f;
+    const float sbin = s16(part);
+    if (lane == bb) hist += sbin;
+  }
+  return hist;
+}
+
+// The same one hash level at a time (mr_levels.h): training rays are as
+// incoherent as bounce rays.  Without a segment in the box a ray's range and
+// histogram are zeros.  4 096 / 8 192 / 16 384 / 65 536 rays of 256 intervals
+// took 376 / 720 / 1 418 / 5 611 us in k_prop_targets and 372 / 524 / 887 /
+// 2 860 so; with 64 intervals 4 096 / 16 384 took 160 / 559 and 189 / 397.
+constexpr int64_t kTargetsLvMin = 6144;
+
+template <typename TabT, bool BF>
+__global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_prop_targets_lv(
+    FieldView F, const TabT* __restrict__ table, const uint32_t* __restrict__ frags, int n, const float* __restrict__ o,
+    const float* __restrict__ d, float t_near, float t_far, int n_samples, int n_bins, float* __restrict__ lohi,
+    float* __restrict__ target, double* __restrict__ scratch, int* __restrict__ pace, int* __restrict__ work) {
+  constexpr int NL = 16;
+  using LY = FragLayout<NL, 16, 2, BF>;
+  __shared__ __align__(16) uint32_t sW[LY::C1];   // the density layers
+  __shared__ LvBatch B;
+  for (int i = threadIdx.x; i < LY::C1; i += kLvThreads) sW[i] = frags[i];
+  const int lane = threadIdx.x & 63, j = lane & 15;
+  const float delta = (t_far - t_near) / (float)n_samples;
+  double* my = scratch + (int64_t)blockIdx.x * kLvSamples * NL;
+  LvPace pc(pace);
+  const int grab = lv_grab(n);
+  int cur = 0, end = 0;
+  while (true) {
+    if (threadIdx.x < 64)
+      B.take(work, n, grab, cur, end, [&](int r, RaySeg& S) {
+        S.ox = o[3 * r]; S.oy = o[3 * r + 1]; S.oz = o[3 * r + 2];
+        S.dx = d[3 * r]; S.dy = d[3 * r + 1]; S.dz = d[3 * r + 2];
+        S.t_a = t_near;
+        float box0, box1;
+        S.lo = S.hi = 0.0f;
+        if (seg_box(F, S.ox, S.oy, S.oz, S.dx, S.dy, S.dz, box0, box1)) {
+          S.lo = fmaxf(t_near, box0);
+          S.hi = fminf(t_far, box1);
+        }
+        const bool hit = S.hi > S.lo;
+        lohi[2 * r] = hit ? S.lo : 0.0f;
+        lohi[2 * r + 1] = hit ? S.hi : 0.0f;
+        if (!hit) {
+          for (int b = 0; b < n_bins; ++b) target[(int64_t)r * n_bins + b] = 0.0f;
+          return false;
+        }
+        S.k0 = max(0, (int)floorf((S.lo - t_near) / delta) - 1);
+        S.k1 = min(n_samples, (int)ceilf((S.hi - t_near) / delta) + 1);
+        return true;
+      });
+    __syncthreads();
+    if (B.n_tiles == 0) break;
+    B.encode<NL, TabT>(F, table, pc, delta, false, my);
+    for (int k = B.next_ray(); k >= 0; k = B.next_ray()) {
+      const int t0 = B.tile0[k], nt = (B.k1[k] - B.k0[k] + 15) / 16;
+      const float lo = B.lo[k], hi = B.hi[k], bw = (hi - lo) / (float)n_bins;
+      float hist = 0.0f, Tseg = 1.0f;   // lane b < n_bins accumulates bin b
+      d4v ahead = lv_load(my, t0, lane);
+      for (int t = 0; t < nt; ++t) {
+        const uint32_t m = B.mask[t0 + t];
+        const bool valid = (m >> j) & 1u;
+        float fe[LY::NF];
+        lv_features(ahead, valid, fe);
+        ahead = lv_load(my, t0 + t + 1, lane);
+        if (m == 0) continue;
+        const int s = B.k0[k] + 16 * t + j;
+        const float a = fmaxf(t_near + (float)s * delta, lo), b = fminf(t_near + (float)(s + 1) * delta, hi), D = b - a;
+        const f4v raw = density_raw<NL, 16, 2, BF>(sW, fe, lane);
+        const float sigma = softplusf(__shfl(raw[0], j, 64) + F.density_offset);
+        const float alpha = valid ? -expm1f(-sigma * D) : 0.0f;
+        const float incl = sc16_mul(1.0f - alpha, j);
+        float excl = __shfl_up(incl, 1, 16);
+        if (j == 0) excl = 1.0f;
+        const float w = Tseg * excl * alpha;
+        Tseg *= __shfl(incl, 15, 16);
+        hist += tile_bins(a, b, D, w, valid, lo, bw, n_bins, lane);
+      }
+      if (lane < n_bins) target[(int64_t)B.r[k] * n_bins + lane] = hist;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) pc.leave();
+}
+
 template <int NL, int SH, int CL, typename TabT, bool BF>
 __global__ __launch_bounds__(256) void k_prop_targets(FieldView F, const TabT* __restrict__ table,
                                                       const uint32_t* __restrict__ frags, int64_t n,
@@ -496,17 +593,7 @@ __global__ __launch_bounds__(256) void k_prop_targets(FieldView F, const TabT* _
         if (j == 0) excl = 1.0f;
         const float w = Tseg * excl * alpha;
         Tseg *= __shfl(incl, 15, 16);
-        // bins touched by this tile
-        const float ta = __shfl(a, 0, 64), tb = __shfl(b, 15, 64);
-        const int bmin = max(0, (int)floorf((ta - lo) / bw) - 1);
-        const int bmax = min(n_bins - 1, (int)floorf((tb - lo) / bw) + 1);
-        for (int bb = bmin; bb <= bmax; ++bb) {
-          const float c0 = lo + (float)bb * bw, c1 = lo + (float)(bb + 1) * bw;
-          const float ov = fminf(b, c1) - fmaxf(a, c0);
-          const float part = (valid && ov > 0.0f) ? w * ov / D : 0.0f;
-          const float sbin = s16(part);
-          if (lane == bb) hist += sbin;
-        }
+        hist += tile_bins(a, b, D, w, valid, lo, bw, n_bins, lane);
       }
     }
     if (lane == 0) {
@@ -724,6 +811,18 @@ template <int NL, int SH, int CL, typename TabT, bool BF>
 mr_status launch_targets(const mr_field* f, int64_t n, const float* o, const float* d, float t_near, float t_far,
                          int n_samples, int n_bins, float* lohi, float* target, hipStream_t st) {
   const uint32_t* fr = BF ? f->frag_bf16_dev : f->frag_f32_dev;
+  if constexpr (NL == 16) {
+    LvScratch lv;
+    if (n >= kTargetsLvMin && n < (1 << 30) && lv_field(f) && lv_lease(st, &lv)) {
+      hipLaunchKernelGGL((k_prop_targets_lv<TabT, BF>), dim3(lv_blocks()), dim3(kLvThreads), 0, st, f->view,
+                         reinterpret_cast<const TabT*>(f->table_dev), fr, (int)n, o, d, t_near, t_far, n_samples, n_bins,
+                         lohi, target, lv.feat, lv.pace, lv.pace + kLvPaceInts);
+      const hipError_t e = hipGetLastError();
+      lv_return(st, lv);
+      MR_HIP(e);
+      return MR_OK;
+    }
+  }
   const int blocks = (int)std::min<int64_t>((n + 3) / 4, (int64_t)device_cus() * 8);
   hipLaunchKernelGGL((k_prop_targets<NL, SH, CL, TabT, BF>), dim3(blocks), dim3(256), 0, st, f->view,
                      reinterpret_cast<const TabT*>(f->table_dev), fr, n, o, d, t_near, t_far, n_samples, n_bins, lohi,

@@ -139,3 +139,18 @@ def test_light_samples_level_by_level(depth_samples, half, occ):
     b = _render(F, G, o, d, sc, opts, lean=True)
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n,n_samples,bins,half", [(6143, 256, 32, False), (6144, 256, 32, False), (9001, 61, 20, True),
+                                                   (20011, 7, 64, False), (6500, 4096, 1, False)])
+def test_targets_level_by_level(n, n_samples, bins, half):
+    F = M.Field(sg.mid_field(9, 0.5, -1.0), **(dict(table_dtype=M.MR_F16, mlp_dtype=M.MR_BF16) if half else {}))
+    T = M.ProposalTrainer(M.Field(sg.make_proposal()), n_bins=bins)
+    o, d = (torch.from_numpy(a).cuda() for a in sg.random_rays(n, seed=n))
+    d[::7] = -d[::7]   # rays that miss the box
+    lohi, tgt = T.targets(F, o, d, 0.05, 4.0, n_samples)
+    parts = [T.targets(F, o[i:i + 3000].contiguous(), d[i:i + 3000].contiguous(), 0.05, 4.0, n_samples)
+             for i in range(0, n, 3000)]
+    assert torch.equal(lohi, torch.cat([p[0] for p in parts]))
+    assert torch.equal(tgt, torch.cat([p[1] for p in parts]))
+    assert (lohi[::7] == 0).all() and tgt.isfinite().all()
