@@ -620,6 +620,10 @@ constexpr int kPropL0Lds = 2 * 17 * 17 * 17;
 // through a per-wave LDS stage whose row strides (17, 11) keep both the
 // row-wise writes and the column-wise operand reads free of bank conflicts.
 constexpr int kStA = 17, kStF = 11, kStageWave = 64 * (kStA + kStF);
+// The table scatter goes four lanes per sample through the same stage (kernel
+// body); a lane per sample made 64 scattered atomics per sample and 35 G/s of
+// them bound the kernel: 1 320 us for 16 384 segments of 32 bins, now 412.
+constexpr int kStG = 13;   // point and feature gradients of a sample
 
 __global__ __launch_bounds__(256) void k_prop_grad(FieldView P, const float* __restrict__ table,
                                                    const float* __restrict__ mlp, int64_t n,
@@ -631,6 +635,7 @@ __global__ __launch_bounds__(256) void k_prop_grad(FieldView P, const float* __r
   __shared__ float sM[16 * 16];
   __shared__ float sL0[kPropL0Lds];
   __shared__ float sStage[4 * kStageWave];
+  __shared__ double sLoss[4];
   for (int i = threadIdx.x; i < kPropMlp; i += blockDim.x) sW[i] = mlp[i];
   for (int i = threadIdx.x; i < 16 * 16; i += blockDim.x) sM[i] = 0.0f;
   const int n1 = P.res[0] + 1;
@@ -642,7 +647,7 @@ __global__ __launch_bounds__(256) void k_prop_grad(FieldView P, const float* __r
   float* sF = sA + 64 * kStA;
   const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
   const size_t T = (size_t)P.table_mask + 1u;
-  float wave_loss = 0.0f;
+  double my_loss = 0.0;
   f4v accM = {0.0f, 0.0f, 0.0f, 0.0f};
   for (int64_t s = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); s < n; s += waves) {
     const float lo = lohi[2 * s], hi = lohi[2 * s + 1];
@@ -667,7 +672,7 @@ __global__ __launch_bounds__(256) void k_prop_grad(FieldView P, const float* __r
     const float rres = h - w;
     float gl = 0.0f;
     if (act && rres > 0.0f) {
-      wave_loss += rres * rres / (h + 1e-7f);
+      my_loss += (double)(rres * rres / (h + 1e-7f));
       gl = -2.0f * rres / (h + 1e-7f) * inv_n;
     }
     // dL/dsigma_k = g_k T_k D exp(-sigma_k D) - D sum_{j > k} g_j w_j
@@ -694,50 +699,72 @@ __global__ __launch_bounds__(256) void k_prop_grad(FieldView P, const float* __r
       accM = mma(a, b, accM);
     }
     wave_lds_sync();
-    if (dz == 0.0f) continue;
     float df[kPropIn];
 #pragma unroll
     for (int c = 0; c < kPropIn; ++c) df[c] = 0.0f;
+    if (dz != 0.0f) {
 #pragma unroll
-    for (int i = 0; i < kPropHidden; ++i) {
-      if (hpre[i] > 0.0f) {
-        const float dh = dz * sW[kPropIn * kPropHidden + i];
+      for (int i = 0; i < kPropHidden; ++i) {
+        if (hpre[i] > 0.0f) {
+          const float dh = dz * sW[kPropIn * kPropHidden + i];
 #pragma unroll
-        for (int c = 0; c < kPropIn; ++c) df[c] += dh * sW[i * kPropIn + c];
+          for (int c = 0; c < kPropIn; ++c) df[c] += dh * sW[i * kPropIn + c];
+        }
       }
     }
     // scatter to the table entries of the 8 corners of every level
     float xh, yh, zh;
     to_unit(P, px, py, pz, xh, yh, zh);
-#pragma unroll
-    for (int l = 0; l < kPropLevels; ++l) {
+    if (n_l0 && dz != 0.0f) {
       uint32_t idx[8];
       float wc[8];
-      level_corners(P, l, xh, yh, zh, idx, wc);
-      if (l == 0 && n_l0) {
-        // two branches rather than one pointer, so these stay LDS atomics
+      level_corners(P, 0, xh, yh, zh, idx, wc);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          atomicAdd(sL0 + 2 * idx[c], wc[c] * df[0]);
-          atomicAdd(sL0 + 2 * idx[c] + 1, wc[c] * df[1]);
-        }
-      } else {
-        float* gt = g_table + (size_t)l * T * 2;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          atomicAdd(gt + 2 * (size_t)idx[c], wc[c] * df[2 * l]);
-          atomicAdd(gt + 2 * (size_t)idx[c] + 1, wc[c] * df[2 * l + 1]);
-        }
+      for (int c = 0; c < 8; ++c) {
+        atomicAdd(sL0 + 2 * idx[c], wc[c] * df[0]);
+        atomicAdd(sL0 + 2 * idx[c] + 1, wc[c] * df[1]);
       }
     }
+    // the other levels four lanes per sample: one atomic instruction covers the
+    // two features of the two x corners of a (y, z) row, neighbouring words of
+    // one line 15 times of 16, for 16 samples
+    float* my = sA + lane * kStG;
+    my[0] = xh; my[1] = yh; my[2] = zh;
+#pragma unroll
+    for (int c = 0; c < kPropIn; ++c) my[3 + c] = df[c];
+    wave_lds_sync();
+    const int hx = (lane >> 1) & 1, ft = lane & 1;
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+      const float* from = sA + (16 * t + (lane >> 2)) * kStG;
+      const float ux = from[0], uy = from[1], uz = from[2];
+#pragma unroll
+      for (int l = 0; l < kPropLevels; ++l) {
+        const float dfl = from[3 + 2 * l + ft];
+        if ((l == 0 && n_l0) || dfl == 0.0f) continue;
+        uint32_t idx[8];
+        float wc[8];
+        level_corners(P, l, ux, uy, uz, idx, wc);
+        float* gt = g_table + (size_t)l * T * 2 + ft;
+#pragma unroll
+        for (int c = 0; c < 8; c += 2)
+          atomicAdd(gt + 2 * (size_t)(hx ? idx[c + 1] : idx[c]), (hx ? wc[c + 1] : wc[c]) * dfl);
+      }
+    }
+    wave_lds_sync();
   }
-  wave_loss = wsum(wave_loss);
-  if (lane == 0 && wave_loss != 0.0f) atomicAdd(loss, wave_loss * inv_n);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) my_loss += __shfl_xor(my_loss, off, 64);
+  if (lane == 0) sLoss[threadIdx.x >> 6] = my_loss;
   // accumulator register v of lane (g, j) holds M[4 g + v][j]
 #pragma unroll
   for (int v = 0; v < 4; ++v)
     if (j < kPropIn && accM[v] != 0.0f) atomicAdd(&sM[(4 * g + v) * 16 + j], accM[v]);
   __syncthreads();
+  if (threadIdx.x == 0) {
+    const double block_loss = (sLoss[0] + sLoss[1]) + (sLoss[2] + sLoss[3]);
+    if (block_loss != 0.0) atomicAdd(loss, (float)(block_loss * inv_n));
+  }
   for (int i = threadIdx.x; i < kPropMlp; i += blockDim.x) {
     float gv = 0.0f;
     if (i < kPropIn * kPropHidden) {
@@ -837,7 +864,7 @@ mr_status grad_into(const mr_field* p, int64_t n, const float* o, const float* d
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(256), 0, st, g_mlp, (int64_t)kPropMlp, 0.0f);
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, loss, (int64_t)1, 0.0f);
   MR_HIP(hipGetLastError());
-  const int blocks = (int)std::min<int64_t>((n + 3) / 4, (int64_t)device_cus() * 8);
+  const int blocks = (int)std::min<int64_t>((n + 3) / 4, (int64_t)device_cus() * 2);   // 69 KB of LDS: two blocks per CU
   hipLaunchKernelGGL(k_prop_grad, dim3(blocks), dim3(256), 0, st, p->view, p->master_dev, p->mlp_dev, n, o, d, lohi,
                      target, n_bins, 1.0f / (float)n, g_table, g_mlp, loss);
   MR_HIP(hipGetLastError());
