@@ -121,30 +121,63 @@ __device__ __forceinline__ void level_corners(const FieldView& F, int l, float x
     w[c] = ((c & 1) ? wx : 1.0f - wx) * ((c & 2) ? wy : 1.0f - wy) * ((c & 4) ? wz : 1.0f - wz);
 }
 
+// Entry at a byte offset from a wave-uniform base.
+template <typename TabT>
+__device__ __forceinline__ float2 load_at(const TabT* __restrict__ tab, uint32_t byte) {
+  return load_entry<TabT>(reinterpret_cast<const TabT*>(reinterpret_cast<const char*>(tab) + byte), 0u);
+}
+
+// The two features of level l at a unit-cube point.  Entries are addressed by
+// 32-bit byte offsets from the table (at most 2^31 bytes), which a load takes
+// beside its scalar base.
+template <typename TabT>
+__device__ __forceinline__ void encode_level(const FieldView& F, const TabT* __restrict__ table, float xh, float yh,
+                                             float zh, int l, float& f0, float& f1) {
+  constexpr int kShift = sizeof(TabT) == 4 ? 3 : 2;   // log2 of an entry's bytes
+  const uint32_t mask = F.table_mask;
+  const int N = F.res[l];
+  const float fN = (float)N, top = fN - 1.0f;
+  const float fx = xh * fN, fy = yh * fN, fz = zh * fN;
+  const float flx = fminf(floorf(fx), top), fly = fminf(floorf(fy), top), flz = fminf(floorf(fz), top);
+  const uint32_t vx = (uint32_t)flx, vy = (uint32_t)fly, vz = (uint32_t)flz;
+  const float wx = fx - flx, wy = fy - fly, wz = fz - flz;
+  const uint32_t base = (uint32_t)l * ((mask + 1u) << kShift);   // at most 2^31 bytes
+  uint32_t off[8];
+  if ((F.dense_mask >> l) & 1u) {
+    const uint32_t n1 = (uint32_t)N + 1u, n2 = __umul24(n1, n1);
+    const uint32_t i = ((vx + __umul24(vy, n1) + __umul24(vz, n2)) << kShift) + base;
+    const uint32_t s1 = n1 << kShift, s2 = n2 << kShift;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) off[c] = i + (c & 1) * (1u << kShift) + ((c >> 1) & 1) * s1 + (c >> 2) * s2;
+  } else {
+    // only the low bits of the products are kept (the table has at most 2^24
+    // entries and N is at most 2^20), so 24-bit multiplies serve
+    const uint32_t py = 2654435761u & mask, pz = 805459861u & mask;
+    const uint32_t hy = __umul24(vy, py), hz = __umul24(vz, pz);
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      off[c] = ((((vx + (c & 1)) ^ ((hy + ((c >> 1) & 1) * py) ^ (hz + (c >> 2) * pz))) & mask) << kShift) + base;
+  }
+  float2 e[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) e[c] = load_at<TabT>(table, off[c]);
+  f0 = 0.0f;
+  f1 = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const float w = ((c & 1) ? wx : 1.0f - wx) * ((c & 2) ? wy : 1.0f - wy) * ((c & 4) ? wz : 1.0f - wz);
+    f0 += w * e[c].x;
+    f1 += w * e[c].y;
+  }
+}
+
 template <int NL, typename TabT>
 __device__ __forceinline__ void hash_encode(const FieldView& F, const TabT* __restrict__ table,
                                             float px, float py, float pz, float* feat) {
   float xh, yh, zh;
   to_unit(F, px, py, pz, xh, yh, zh);
-  const size_t T = (size_t)F.table_mask + 1u;
 #pragma unroll
-  for (int l = 0; l < NL; ++l) {
-    uint32_t idx[8];
-    float w[8];
-    level_corners(F, l, xh, yh, zh, idx, w);
-    const TabT* tab = table + (size_t)l * T * 2;
-    float2 e[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = load_entry<TabT>(tab, idx[c]);
-    float f0 = 0.0f, f1 = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      f0 += w[c] * e[c].x;
-      f1 += w[c] * e[c].y;
-    }
-    feat[2 * l] = f0;
-    feat[2 * l + 1] = f1;
-  }
+  for (int l = 0; l < NL; ++l) encode_level<TabT>(F, table, xh, yh, zh, l, feat[2 * l], feat[2 * l + 1]);
 }
 
 // Real orthonormal SH (Sloan's ordering, Condon-Shortley phase), n = 4 or 16.

@@ -116,11 +116,25 @@ __device__ __forceinline__ uint4 pack_bf16(const f4v& lo, const f4v& hi) {
 // 2^-16 of its size and drops at most 2^-26 of it, under the 2^-24 rounding
 // of an FP32 product; the matrix cores form each BF16 product exactly and sum
 // in FP32 (the bf16x6 scheme of Henry, Tang and Heinecke, ARITH 2019).
+// The residual a - a0 is one v_dot2c_f32_bf16 (products and sum exact) with the
+// pair (-1, 0) or (0, -1): 7 instructions per pair instead of 11.  The low
+// unit lives in a scalar register: as an inline constant -1.0 would land in
+// the high half.  A pair with an infinity gives NaN residuals for both of its
+// values, which belong to one sample, whose products are NaN anyway.
+__device__ __forceinline__ float minus_low(uint32_t p, float a) {
+  uint32_t unit;
+  asm("s_mov_b32 %0, 0xbf80" : "=s"(unit));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), __builtin_bit_cast(bf16x2_t, unit), a, false);
+}
+__device__ __forceinline__ float minus_high(uint32_t p, float b) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), __builtin_bit_cast(bf16x2_t, 0xBF800000u), b,
+                                         false);
+}
 __device__ __forceinline__ void split3(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
   p0 = pack2_bf16(a, b);
-  const float ra = a - __uint_as_float(p0 << 16), rb = b - __uint_as_float(p0 & 0xFFFF0000u);
+  const float ra = minus_low(p0, a), rb = minus_high(p0, b);
   p1 = pack2_bf16(ra, rb);
-  p2 = pack2_bf16(ra - __uint_as_float(p1 << 16), rb - __uint_as_float(p1 & 0xFFFF0000u));
+  p2 = pack2_bf16(minus_low(p1, ra), minus_high(p1, rb));
 }
 __device__ __forceinline__ void split3(float a, float b, float c, float d, uint2& p0, uint2& p1, uint2& p2) {
   split3(a, b, p0.x, p1.x, p2.x);
@@ -161,47 +175,8 @@ __device__ __forceinline__ void encode_group(const FieldView& F, const TabT* __r
   constexpr int LPG = NL / 4;
   float xh, yh, zh;
   to_unit(F, px, py, pz, xh, yh, zh);
-  const size_t T = (size_t)F.table_mask + 1u;
 #pragma unroll
-  for (int ll = 0; ll < LPG; ++ll) {
-    const int l = ll * 4 + g;
-    uint32_t idx[8];
-    float w[8];
-    level_corners(F, l, xh, yh, zh, idx, w);
-    const TabT* tab = table + (size_t)l * T * 2;
-    float2 e[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = load_entry<TabT>(tab, idx[c]);
-    float f0 = 0.0f, f1 = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      f0 += w[c] * e[c].x;
-      f1 += w[c] * e[c].y;
-    }
-    fe[2 * ll] = f0;
-    fe[2 * ll + 1] = f1;
-  }
-}
-
-// The two features of level l at a unit-cube point (one level of encode_group).
-template <typename TabT>
-__device__ __forceinline__ void encode_level(const FieldView& F, const TabT* __restrict__ table, float xh, float yh,
-                                             float zh, int l, float& f0, float& f1) {
-  const size_t T = (size_t)F.table_mask + 1u;
-  uint32_t idx[8];
-  float w[8];
-  level_corners(F, l, xh, yh, zh, idx, w);
-  const TabT* tab = table + (size_t)l * T * 2;
-  float2 e[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) e[c] = load_entry<TabT>(tab, idx[c]);
-  f0 = 0.0f;
-  f1 = 0.0f;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    f0 += w[c] * e[c].x;
-    f1 += w[c] * e[c].y;
-  }
+  for (int ll = 0; ll < LPG; ++ll) encode_level<TabT>(F, table, xh, yh, zh, ll * 4 + g, fe[2 * ll], fe[2 * ll + 1]);
 }
 
 // One level for the wave's 64 samples, a sample per lane, for loops that keep
@@ -218,12 +193,6 @@ __device__ __forceinline__ uint32_t pair_get(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xF, 0xF, true);
 }
 constexpr int kPairEven = 0xA0, kPairOdd = 0xF5;   // quad_perm [0,0,2,2] and [1,1,3,3]
-
-// Entry at a byte offset within one level's slice.
-template <typename TabT>
-__device__ __forceinline__ float2 load_at(const TabT* __restrict__ tab, uint32_t byte) {
-  return load_entry<TabT>(reinterpret_cast<const TabT*>(reinterpret_cast<const char*>(tab) + byte), 0u);
-}
 
 template <typename TabT>
 __device__ __forceinline__ float2 encode_level_pair(const FieldView& F, const TabT* __restrict__ table, int l, int lane,
