@@ -96,7 +96,8 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
       });
     __syncthreads();
     if (B.n_tiles == 0) break;
-    B.encode<NL, TabT>(F, table, pc, delta, use_occ, my);
+    B.encode<NL, TabT>(F, table, pc, use_occ, my,
+                       [&](int i, float& px, float& py, float& pz) { return B.place(i, delta, px, py, pz); });
     for (int k = B.next_ray(); k >= 0; k = B.next_ray()) {
       const int t0 = B.tile0[k], nt = (B.k1[k] - B.k0[k] + 15) / 16;
       const float lo = B.lo[k], hi = B.hi[k];

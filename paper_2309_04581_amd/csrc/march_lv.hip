@@ -36,7 +36,8 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
       B.take(work, cnt, grab, cur, end, [&](int r, RaySeg& S) { return ray_seg(q, r, F, P, S); });
     __syncthreads();
     if (B.n_tiles == 0) break;
-    B.encode<NL, TabT>(F, table, pc, delta, P.use_occupancy && F.occ, my);
+    B.encode<NL, TabT>(F, table, pc, P.use_occupancy && F.occ, my,
+                       [&](int i, float& px, float& py, float& pz) { return B.place(i, delta, px, py, pz); });
     // MLP tiles and compositing, a ray per wave
     for (int k = B.next_ray(); k >= 0; k = B.next_ray()) {
       const int t0 = B.tile0[k], nt = (B.k1[k] - B.k0[k] + 15) / 16;
@@ -196,7 +197,18 @@ namespace mr {
 
 int lv_blocks() { return 2 * ((device_cus() + kXcds - 1) / kXcds) * kXcds; }
 
-size_t lv_bytes() { return kLvPaceArea + (size_t)lv_blocks() * kLvSamples * 16 * sizeof(double); }
+size_t lv_bytes() {
+  return kLvPaceArea + (size_t)lv_blocks() * kLvSamples * (16 * sizeof(double) + sizeof(float));
+}
+
+LvScratch lv_scratch(void* area, int launch) {
+  char* c = reinterpret_cast<char*>(area);
+  LvScratch lv;
+  lv.pace = reinterpret_cast<int*>(c) + (size_t)launch * kLvPaceInts;
+  lv.feat = reinterpret_cast<double*>(c + kLvPaceArea);
+  lv.edge = reinterpret_cast<float*>(lv.feat + (size_t)lv_blocks() * kLvSamples * 16);
+  return lv;
+}
 
 bool lv_field(const mr_field* f) {
   const auto& v = f->view;
@@ -234,8 +246,7 @@ bool lv_lease(hipStream_t st, LvScratch* lv) {
     (void)hipGetLastError();
     return false;
   }
-  lv->pace = reinterpret_cast<int*>(p);
-  lv->feat = reinterpret_cast<double*>(reinterpret_cast<char*>(p) + kLvPaceArea);
+  *lv = lv_scratch(p, 0);
   hipLaunchKernelGGL(k_zero_pace, dim3(1), dim3(kLvPaceInts), 0, st, lv->pace);
   return true;
 }

@@ -186,29 +186,33 @@ struct LvBatch {
     }
   }
 
-  // Sample i (tile * 16 + column): its interval [a, b] and point; false if the
-  // ray has no such sample.
-  __device__ __forceinline__ bool place(int i, float delta, float& a, float& b, float& px, float& py, float& pz) const {
-    const int t = i >> 4, k = ray_of[t], s = k0[k] + 16 * (t - tile0[k]) + (i & 15);
-    const float ta = t_a[k];
-    a = fmaxf(ta + (float)s * delta, lo[k]);
-    b = fminf(ta + (float)(s + 1) * delta, hi[k]);
+  // Point of the batch's ray k in the middle of [a, b].
+  __device__ __forceinline__ void middle(int k, float a, float b, float& px, float& py, float& pz) const {
     const float tm = 0.5f * (a + b);
     px = ox[k] + tm * dx[k];
     py = oy[k] + tm * dy[k];
     pz = oz[k] + tm * dz[k];
+  }
+  // Sample i (tile * 16 + column) on the uniform grid of spacing delta; false
+  // if the ray has no such sample.
+  __device__ __forceinline__ bool place(int i, float delta, float& px, float& py, float& pz) const {
+    const int t = i >> 4, k = ray_of[t], s = k0[k] + 16 * (t - tile0[k]) + (i & 15);
+    const float ta = t_a[k];
+    const float a = fmaxf(ta + (float)s * delta, lo[k]), b = fminf(ta + (float)(s + 1) * delta, hi[k]);
+    middle(k, a, b, px, py, pz);
     return s < k1[k] && b > a;
   }
 
-  // The whole block: the batch's valid samples and their features.
-  template <int NL, typename TabT>
-  __device__ __forceinline__ void encode(const FieldView& F, const TabT* __restrict__ table, LvPace& pc, float delta,
-                                         bool use_occ, double* __restrict__ out) {
+  // The whole block: the batch's valid samples and their features.  at(i, px,
+  // py, pz) gives sample i's point, false if there is none.
+  template <int NL, typename TabT, typename At>
+  __device__ __forceinline__ void encode(const FieldView& F, const TabT* __restrict__ table, LvPace& pc, bool use_occ,
+                                         double* __restrict__ out, At at) {
     const int lane = threadIdx.x & 63, j = lane & 15, samples = n_tiles * 16;
     for (int i0 = threadIdx.x & ~63; i0 < samples; i0 += kLvThreads) {
       const int i = i0 + lane;
-      float a, b, px, py, pz;
-      bool valid = i < samples && place(i, delta, a, b, px, py, pz);
+      float px, py, pz;
+      bool valid = i < samples && at(i, px, py, pz);
       if (valid && use_occ) valid = occ_lookup(F, px, py, pz);
       const uint64_t m = __ballot(valid);
       if (j == 0 && i < samples) mask[i >> 4] = (uint32_t)(m >> (lane & 48)) & 0xFFFFu;
@@ -226,8 +230,8 @@ struct LvBatch {
 #pragma unroll
       for (int it = 0; it < kLvPer; ++it) {
         const int e = it * kLvThreads + threadIdx.x, i = list[min(e, nv - 1)];
-        float a, b, px, py, pz;
-        place(i, delta, a, b, px, py, pz);
+        float px, py, pz;
+        at(i, px, py, pz);
         to_unit(F, px, py, pz, xh[it], yh[it], zh[it]);
         dst[it] = e < nv ? (i >> 4) * NL * 16 + (i & 15) : -1;
       }

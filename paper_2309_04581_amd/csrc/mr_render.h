@@ -39,7 +39,7 @@ struct MarchParams {
   // rays are then left without this segment's medium)
   int wait_polls;
   int* gave_up;
-  int lv;             // queues of kLvMinRays or more are marched by k_march_lv
+  int lv;             // queues of kLvMinRays or more are marched level by level
 };
 
 // Shadow mask of the sample of column j (Sec. 3.1 "Shadow rays"): a lane of
@@ -157,7 +157,7 @@ mr_status dispatch_march_fields(const mr_field* const* fields, int n_fields, Ray
 // march of incoherent segments level by level (march_lv.hip); it leaves queues
 // of fewer than kLvMinRays rays alone.  Its scratch in the workspace: kLvPaceArea
 // bytes of pacing counters, kLvPaceInts for each launch and zeroed with the
-// header, then the features of the blocks' batches.
+// header, then the features of the blocks' batches and a value per sample.
 constexpr int kLvSamples = 4096;   // samples per batch
 // Below this queue length the per-ray march is as fast (mid frames of 128 to
 // 800 pixels a side); frames of fewer than kLvMinFrame rays hardly have such
@@ -170,7 +170,9 @@ constexpr size_t kLvPaceArea = 2 * (size_t)(kMaxBounces + 2) * kLvPaceInts * siz
 struct LvScratch {
   int* pace;      // this launch's counters
   double* feat;   // (feature 0, feature 1) pairs
+  float* edge;    // a value per sample (interval edges of the proposal march)
 };
+LvScratch lv_scratch(void* area, int launch);   // of the lv_bytes() at area
 int lv_blocks();
 size_t lv_bytes();
 // Point queries go level by level from this many points: 50 000 / 100 000 / 1 M
@@ -208,9 +210,11 @@ mr_status dispatch_light_march(const mr_field* f, RayQueue q, RayQueue next, con
                                hipStream_t st);
 
 // proposal-sampled march (defined with the proposal kernels)
-// packets: 16 consecutive queue rays per wave when n_prop = 32 and n_fine <= 32
+// packets: 16 consecutive queue rays per wave when n_prop = 32 and n_fine <= 32.
+// P.lv: queues of kLvMinRays or more go level by level, with scratch lv
 mr_status dispatch_march_proposal(const mr_field* f, const mr_field* prop, RayQueue q, const int* count, int* work,
                                   const MarchParams& P, const BvhView& B, int n_prop, int n_fine, bool packets,
-                                  unsigned long long* stats, int blocks_per_cu, int64_t n, hipStream_t st);
+                                  unsigned long long* stats, int blocks_per_cu, int64_t n, const LvScratch& lv,
+                                  hipStream_t st);
 
 }  // namespace mr

@@ -14,6 +14,7 @@
 // plain marcher's weights over the same n_p bins.
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "mr_field_kernels.h"
@@ -26,25 +27,29 @@ namespace {
 constexpr int kPropLevels = 5;
 constexpr int kPropIn = 10, kPropHidden = 16, kPropMlp = kPropIn * kPropHidden + kPropHidden;
 
+// Inclusive scans and sums over groups of W lanes.
+template <int W = 64>
 __device__ __forceinline__ float wscan_mul(float v, int lane) {
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const float u = __shfl_up(v, off, 64);
+  for (int off = 1; off < W; off <<= 1) {
+    const float u = __shfl_up(v, off, W);
     if (lane >= off) v *= u;
   }
   return v;
 }
+template <int W = 64>
 __device__ __forceinline__ float wscan_add(float v, int lane) {
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const float u = __shfl_up(v, off, 64);
+  for (int off = 1; off < W; off <<= 1) {
+    const float u = __shfl_up(v, off, W);
     if (lane >= off) v += u;
   }
   return v;
 }
+template <int W = 64>
 __device__ __forceinline__ float wsum(float v) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  for (int off = W / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 __device__ __forceinline__ float sc16_mul(float v, int j) {
@@ -130,6 +135,55 @@ __device__ __forceinline__ float prop_sigma(const FieldView& P, const TabT* __re
   return softplusf(acc + P.density_offset);
 }
 
+// Edge `lane` of the fine intervals of [lo, hi] on a ray, by the inverse CDF of
+// the proposal weights: W lanes per ray (64, or 32 for at most 32 proposal and
+// fine intervals: the same tree of the scans, the same bits), a proposal
+// interval per lane.
+template <int W, typename PTabT>
+__device__ __forceinline__ float fine_edge(const FieldView& Pf, const PTabT* __restrict__ ptable,
+                                           const float* __restrict__ sP, float ox, float oy, float oz, float dx,
+                                           float dy, float dz, float lo, float hi, int n_prop, int n_fine, int lane) {
+  // proposal weights on n_prop uniform intervals
+  const float Dp = (hi - lo) / (float)n_prop;
+  float alpha_p = 0.0f;
+  if (lane < n_prop) {
+    const float tm = lo + ((float)lane + 0.5f) * Dp;
+    const float sp = prop_sigma<PTabT>(Pf, ptable, sP, ox + tm * dx, oy + tm * dy, oz + tm * dz);
+    alpha_p = -expm1f(-sp * Dp);
+  }
+  const float inclT = wscan_mul<W>(1.0f - alpha_p, lane);
+  float exclT = __shfl_up(inclT, 1, W);
+  if (lane == 0) exclT = 1.0f;
+  // dilate over adjacent bins and mix half and half with a uniform density
+  const float wraw = lane < n_prop ? exclT * alpha_p : 0.0f;
+  float wl = __shfl_up(wraw, 1, W), wr = __shfl_down(wraw, 1, W);
+  if (lane == 0) wl = 0.0f;
+  if (lane >= n_prop - 1) wr = 0.0f;
+  const float wdil = lane < n_prop ? fmaxf(wraw, fmaxf(wl, wr)) : 0.0f;
+  const float wmean = wsum<W>(wdil) / (float)n_prop;
+  const float wp = lane < n_prop ? wdil + wmean + 1e-3f / (float)n_prop : 0.0f;
+  const float cdf = wscan_add<W>(wp, lane);
+  const float tot = __shfl(cdf, n_prop - 1, W);
+  // edges of the fine intervals by inverse CDF (lane e holds edge e)
+  const float u = (float)lane / (float)n_fine * tot;
+  int blo = 0, bhi = n_prop - 1;
+#pragma unroll
+  for (int it = 0; it < 6; ++it) {
+    const int mid = (blo + bhi) >> 1;
+    const float cm = __shfl(cdf, mid, W);
+    if (blo < bhi) {
+      if (cm < u) blo = mid + 1;
+      else bhi = mid;
+    }
+  }
+  const float prev = __shfl(cdf, max(blo - 1, 0), W);
+  const float wj = __shfl(wp, blo, W);
+  float edge = lo + ((float)blo + ((blo > 0 ? u - prev : u) / wj)) * Dp;
+  if (lane == 0) edge = lo;
+  if (lane >= n_fine) edge = hi;
+  return edge;
+}
+
 // ---------------------------------------------------------------------------
 // proposal-sampled march (one wave per ray)
 // ---------------------------------------------------------------------------
@@ -140,6 +194,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                                                     const PTabT* __restrict__ ptable, MarchParams P, BvhView B,
                                                     int n_prop, int n_fine, unsigned long long* __restrict__ stats) {
   using LY = FragLayout<NL, SH, CL, BF>;
+  if (P.lv && *count >= kLvMinRays) return;   // k_march_prop_lv takes a long queue
   __shared__ __align__(16) uint32_t sW[LY::TOTAL];
   __shared__ float sP[kPropMlp];
   __shared__ int sstack[4 * 16 * kStack];   // shadow-ray stacks: 16 lanes per wave
@@ -165,44 +220,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const float lo = fmaxf(t_a, box0);
     const float hi = fminf(fminf(t_a + P.span, q.hit_t[r]), box1);
     if (!(hi > lo)) continue;
-    // proposal weights on n_prop uniform intervals
-    const float Dp = (hi - lo) / (float)n_prop;
-    float alpha_p = 0.0f;
-    if (lane < n_prop) {
-      const float tm = lo + ((float)lane + 0.5f) * Dp;
-      const float sp = prop_sigma<PTabT>(Pf, ptable, sP, ox + tm * dx, oy + tm * dy, oz + tm * dz);
-      alpha_p = -expm1f(-sp * Dp);
-    }
-    const float inclT = wscan_mul(1.0f - alpha_p, lane);
-    float exclT = __shfl_up(inclT, 1, 64);
-    if (lane == 0) exclT = 1.0f;
-    // dilate over adjacent bins and mix half and half with a uniform density
-    const float wraw = lane < n_prop ? exclT * alpha_p : 0.0f;
-    float wl = __shfl_up(wraw, 1, 64), wr = __shfl_down(wraw, 1, 64);
-    if (lane == 0) wl = 0.0f;
-    if (lane >= n_prop - 1) wr = 0.0f;
-    const float wdil = lane < n_prop ? fmaxf(wraw, fmaxf(wl, wr)) : 0.0f;
-    const float wmean = wsum(wdil) / (float)n_prop;
-    const float wp = lane < n_prop ? wdil + wmean + 1e-3f / (float)n_prop : 0.0f;
-    const float cdf = wscan_add(wp, lane);
-    const float tot = __shfl(cdf, n_prop - 1, 64);
-    // edges of the fine intervals by inverse CDF (lane e holds edge e)
-    const float u = (float)lane / (float)n_fine * tot;
-    int blo = 0, bhi = n_prop - 1;
-#pragma unroll
-    for (int it = 0; it < 6; ++it) {
-      const int mid = (blo + bhi) >> 1;
-      const float cm = __shfl(cdf, mid, 64);
-      if (blo < bhi) {
-        if (cm < u) blo = mid + 1;
-        else bhi = mid;
-      }
-    }
-    const float prev = __shfl(cdf, max(blo - 1, 0), 64);
-    const float wj = __shfl(wp, blo, 64);
-    float edge = lo + ((float)blo + ((blo > 0 ? u - prev : u) / wj)) * Dp;
-    if (lane == 0) edge = lo;
-    if (lane >= n_fine) edge = hi;
+    const float edge = fine_edge<64, PTabT>(Pf, ptable, sP, ox, oy, oz, dx, dy, dz, lo, hi, n_prop, n_fine, lane);
     // fine samples, 16 per tile
     float u_sh[4][4];
     sh_rows<NL, SH, CL, BF>(sW, dx, dy, dz, lane, u_sh);
@@ -254,6 +272,118 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int off = 32; off > 0; off >>= 1) nsamp += __shfl_xor(nsamp, off, 64);
     if (lane == 0 && nsamp) atomicAdd(stats + 0, nsamp);
   }
+}
+
+// The same with the fine samples one hash level at a time (mr_levels.h), long
+// queues only: the block's waves place the batch's edges first, a ray each at
+// a time.  The same samples, arithmetic and order, the same bits.  Bounce
+// segments of the 800x800 proposal frame (FP16 table, BF16 MLPs): 4.15 -> 3.2 ms.
+template <typename TabT, bool BF, typename PTabT>
+__global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_march_prop_lv(
+    RayQueue q, const int* __restrict__ count, int* __restrict__ work, FieldView F, const TabT* __restrict__ table,
+    const uint32_t* __restrict__ frags, FieldView Pf, const PTabT* __restrict__ ptable, MarchParams P, int n_prop,
+    int n_fine, LvScratch lv, unsigned long long* __restrict__ stats) {
+  constexpr int NL = 16, SH = 16, CL = 2;
+  using LY = FragLayout<NL, SH, CL, BF>;
+  __shared__ __align__(16) uint32_t sW[LY::TOTAL];
+  __shared__ float sP[kPropMlp];
+  __shared__ LvBatch B;
+  const int cnt = *count;
+  if (cnt < kLvMinRays) return;
+  for (int i = threadIdx.x; i < LY::TOTAL; i += kLvThreads) sW[i] = frags[i];
+  for (int i = threadIdx.x; i < kPropMlp; i += kLvThreads) sP[i] = Pf.mlp[i];
+  const int lane = threadIdx.x & 63, j = lane & 15;
+  double* my = lv.feat + (int64_t)blockIdx.x * kLvSamples * NL;
+  float* edges = lv.edge + (int64_t)blockIdx.x * kLvSamples;   // n_fine per ray of the batch
+  const int nt = (n_fine + 15) / 16;
+  LvPace pc(lv.pace);
+  unsigned long long nsamp = 0;
+  const int grab = lv_grab(cnt);
+  int cur = 0, end = 0;
+  while (true) {
+    if (threadIdx.x < 64)
+      B.take(work, cnt, grab, cur, end, [&](int r, RaySeg& S) {
+        S.ox = q.ox[r]; S.oy = q.oy[r]; S.oz = q.oz[r];
+        S.dx = q.dx[r]; S.dy = q.dy[r]; S.dz = q.dz[r];
+        to_field_frame(F, S.ox, S.oy, S.oz, S.dx, S.dy, S.dz);   // the proposal shares the field's frame
+        S.t_a = (q.depth[r] & 0xFFFF) == 0 ? P.t_near : 0.0f;
+        float box0, box1;
+        if (!seg_box(F, S.ox, S.oy, S.oz, S.dx, S.dy, S.dz, box0, box1)) return false;
+        S.lo = fmaxf(S.t_a, box0);
+        S.hi = fminf(fminf(S.t_a + P.span, q.hit_t[r]), box1);
+        S.k0 = 0;
+        S.k1 = n_fine;
+        return S.hi > S.lo;
+      });
+    __syncthreads();
+    if (B.n_tiles == 0) break;
+    auto place = [&](auto width, int k0, int step) {
+      constexpr int W = decltype(width)::value;
+      const int e = lane & (W - 1);
+      // every lane of a wave takes part: a wave's last half may repeat a ray
+      for (int base = k0; base < B.n_rays; base += step) {
+        const int k = min(base + lane / W, B.n_rays - 1);
+        const float v = fine_edge<W, PTabT>(Pf, ptable, sP, B.ox[k], B.oy[k], B.oz[k], B.dx[k], B.dy[k], B.dz[k],
+                                            B.lo[k], B.hi[k], n_prop, n_fine, e);
+        if (e < n_fine) edges[k * n_fine + e] = v;
+      }
+    };
+    const int wave = threadIdx.x >> 6;
+    if (n_prop <= 32 && n_fine <= 32) place(std::integral_constant<int, 32>(), 2 * wave, kLvThreads / 32);
+    else place(std::integral_constant<int, 64>(), wave, kLvThreads / 64);
+    __syncthreads();
+    B.encode<NL, TabT>(F, table, pc, P.use_occupancy && F.occ, my, [&](int i, float& px, float& py, float& pz) {
+      const int t = i >> 4, k = B.ray_of[t], s = 16 * (t - B.tile0[k]) + (i & 15);
+      const float* e = edges + k * n_fine + min(s, n_fine - 1);
+      const float a = e[0], b = s + 1 >= n_fine ? B.hi[k] : e[1];
+      B.middle(k, a, b, px, py, pz);
+      return s < n_fine && b > a;
+    });
+    for (int k = B.next_ray(); k >= 0; k = B.next_ray()) {
+      const int t0 = B.tile0[k];
+      // the ray's throughput (lanes 0..2) and radiance (3..5), needed at its end
+      float* state = q.tr + (int64_t)min(lane, 5) * (q.tg - q.tr) + B.r[k];
+      const float old = *state;
+      const float edge = edges[k * n_fine + min(lane, n_fine - 1)], hi = B.hi[k];
+      float u[4][4];
+      sh_rows<NL, SH, CL, BF>(sW, B.dx[k], B.dy[k], B.dz[k], lane, u);
+      float Tseg = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
+      d4v ahead = lv_load(my, t0, lane);
+      for (int t = 0; t < nt; ++t) {
+        const uint32_t m = B.mask[t0 + t];
+        const bool valid = (m >> j) & 1u;
+        float fe[LY::NF];
+        lv_features(ahead, valid, fe);
+        ahead = lv_load(my, t0 + t + 1, lane);
+        const int s = 16 * t + j;
+        const float a = __shfl(edge, min(s, 63), 64), bn = __shfl(edge, min(s + 1, 63), 64);
+        const float D = (s + 1 >= n_fine ? hi : bn) - a;
+        if (m == 0) continue;
+        float sigma, rgb[3];
+        f4v raw;
+        mlp_tile<NL, SH, CL, BF>(sW, fe, u, F.density_offset, lane, sigma, rgb, raw);
+        const float alpha = valid ? -expm1f(-sigma * D) : 0.0f;
+        const float incl = sc16_mul(1.0f - alpha, j);
+        float excl = __shfl_up(incl, 1, 16);
+        if (j == 0) excl = 1.0f;
+        const float w = Tseg * excl * alpha;
+        acc0 += w * rgb[0];
+        acc1 += w * rgb[1];
+        acc2 += w * rgb[2];
+        Tseg *= __shfl(incl, 15, 16);
+        if (lane == 0) nsamp += __popc(m);
+      }
+      acc0 = s16(acc0);
+      acc1 = s16(acc1);
+      acc2 = s16(acc2);
+      const float tr = __shfl(old, lane >= 3 ? lane - 3 : lane, 64);
+      const float l = lane == 3 ? acc0 : (lane == 4 ? acc1 : acc2);
+      if (lane < 6) *state = lane < 3 ? old * Tseg : old + tr * l;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) pc.leave();
+  if (stats && lane == 0 && nsamp) atomicAdd(stats + 0, nsamp);
 }
 
 // ---------------------------------------------------------------------------
@@ -514,7 +644,8 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
       });
     __syncthreads();
     if (B.n_tiles == 0) break;
-    B.encode<NL, TabT>(F, table, pc, delta, false, my);
+    B.encode<NL, TabT>(F, table, pc, false, my,
+                       [&](int i, float& px, float& py, float& pz) { return B.place(i, delta, px, py, pz); });
     for (int k = B.next_ray(); k >= 0; k = B.next_ray()) {
       const int t0 = B.tile0[k], nt = (B.k1[k] - B.k0[k] + 15) / 16;
       const float lo = B.lo[k], hi = B.hi[k], bw = (hi - lo) / (float)n_bins;
@@ -804,7 +935,8 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float
 template <int NL, int SH, int CL, typename TabT, bool BF, typename PTabT, bool SHADOW>
 mr_status launch_prop_mode(const mr_field* f, const mr_field* p, RayQueue q, const int* count, int* work,
                            const MarchParams& P, const BvhView& B, int n_prop, int n_fine, bool packets,
-                           unsigned long long* stats, int blocks_per_cu, int64_t n, hipStream_t st) {
+                           unsigned long long* stats, int blocks_per_cu, int64_t n, const LvScratch& lv,
+                           hipStream_t st) {
   const uint32_t* fr = BF ? f->frag_bf16_dev : f->frag_f32_dev;
   const TabT* tab = reinterpret_cast<const TabT*>(f->table_dev);
   const PTabT* ptab = reinterpret_cast<const PTabT*>(p->table_dev);
@@ -814,6 +946,12 @@ mr_status launch_prop_mode(const mr_field* f, const mr_field* p, RayQueue q, con
     hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, count, work, f->view, tab, fr, p->view, ptab, P, B,
                        n_fine, stats);
   } else {
+    if constexpr (NL == 16 && !SHADOW)
+      if (P.lv) {
+        hipLaunchKernelGGL((k_march_prop_lv<TabT, BF, PTabT>), dim3(lv_blocks()), dim3(kLvThreads), 0, st, q, count, work,
+                           f->view, tab, fr, p->view, ptab, P, n_prop, n_fine, lv, stats);
+        MR_HIP(hipGetLastError());
+      }
     auto* k = k_march_prop<NL, SH, CL, TabT, BF, PTabT, SHADOW>;
     const int blocks = persistent_blocks(reinterpret_cast<const void*>(k), 256, blocks_per_cu, (n + 3) / 4);
     hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, count, work, f->view, tab, fr, p->view, ptab, P, B,
@@ -826,12 +964,12 @@ mr_status launch_prop_mode(const mr_field* f, const mr_field* p, RayQueue q, con
 template <int NL, int SH, int CL, typename TabT, bool BF, typename PTabT>
 mr_status launch_prop(const mr_field* f, const mr_field* p, RayQueue q, const int* count, int* work,
                       const MarchParams& P, const BvhView& B, int n_prop, int n_fine, bool packets,
-                      unsigned long long* stats, int blocks_per_cu, int64_t n, hipStream_t st) {
+                      unsigned long long* stats, int blocks_per_cu, int64_t n, const LvScratch& lv, hipStream_t st) {
   if (P.shadows)
     return launch_prop_mode<NL, SH, CL, TabT, BF, PTabT, true>(f, p, q, count, work, P, B, n_prop, n_fine, packets,
-                                                               stats, blocks_per_cu, n, st);
+                                                               stats, blocks_per_cu, n, lv, st);
   return launch_prop_mode<NL, SH, CL, TabT, BF, PTabT, false>(f, p, q, count, work, P, B, n_prop, n_fine, packets,
-                                                              stats, blocks_per_cu, n, st);
+                                                              stats, blocks_per_cu, n, lv, st);
 }
 
 template <int NL, int SH, int CL, typename TabT, bool BF>
@@ -886,13 +1024,14 @@ namespace mr {
 
 mr_status dispatch_march_proposal(const mr_field* f, const mr_field* prop, RayQueue q, const int* count, int* work,
                                   const MarchParams& P, const BvhView& B, int n_prop, int n_fine, bool packets,
-                                  unsigned long long* stats, int blocks_per_cu, int64_t n, hipStream_t st) {
+                                  unsigned long long* stats, int blocks_per_cu, int64_t n, const LvScratch& lv,
+                                  hipStream_t st) {
   const auto& v = f->view;
   const bool h = v.table_dtype == MR_F16, bf = v.mlp_dtype == MR_BF16;
   const bool ph = prop->view.table_dtype == MR_F16;
 #define PR(NL, SH, CL, TT, BFV)                                                                                      \
-  return ph ? launch_prop<NL, SH, CL, TT, BFV, __half>(f, prop, q, count, work, P, B, n_prop, n_fine, packets, stats, blocks_per_cu, n, st) \
-            : launch_prop<NL, SH, CL, TT, BFV, float>(f, prop, q, count, work, P, B, n_prop, n_fine, packets, stats, blocks_per_cu, n, st);
+  return ph ? launch_prop<NL, SH, CL, TT, BFV, __half>(f, prop, q, count, work, P, B, n_prop, n_fine, packets, stats, blocks_per_cu, n, lv, st) \
+            : launch_prop<NL, SH, CL, TT, BFV, float>(f, prop, q, count, work, P, B, n_prop, n_fine, packets, stats, blocks_per_cu, n, lv, st);
 #define M(NL, SH, CL)                                                        \
   if (v.n_levels == NL && v.sh == SH && v.c_layers == CL) {                   \
     if (bf) {                                                                 \

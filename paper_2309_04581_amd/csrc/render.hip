@@ -903,16 +903,15 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
   P.gave_up = gave_up;
   // per-ray segments of a large 16-level field go level by level where the
   // workspace has the scratch area for it
-  int* lv_pace = reinterpret_cast<int*>(ws + queues_bytes(n, n_fields));
-  double* lv_feat = reinterpret_cast<double*>(reinterpret_cast<char*>(lv_pace) + kLvPaceArea);
+  char* lv_area = ws + queues_bytes(n, n_fields);
   const bool lv = n_fields == 1 && n >= kLvMinFrame && workspace_bytes >= queues_bytes(n, n_fields) + lv_bytes() &&
                   lv_field(field);
   const bool lv_light = lv && opts->sample_emitters;
-  P.lv = lv && opts->sampler == MR_SAMPLER_UNIFORM && !P.shadows;
+  P.lv = lv && !P.shadows;
 
   const int init_blocks = (int)std::min<int64_t>((n + 255) / 256, 65535);
   hipLaunchKernelGGL(k_init, dim3(init_blocks), dim3(256), 0, st, n, origins, dirs, per_ray_max_bounces, max_bounces,
-                     Q[0], counts, kHeaderCounters, lv_pace, lv ? 2 * (max_bounces + 1) * kLvPaceInts : 0,
+                     Q[0], counts, kHeaderCounters, reinterpret_cast<int*>(lv_area), lv ? 2 * (max_bounces + 1) * kLvPaceInts : 0,
                      out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
   MR_HIP(hipGetLastError());
 
@@ -978,7 +977,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
         if (opts->sampler == MR_SAMPLER_PROPOSAL)
           s = dispatch_march_proposal(fields[k], proposals[k], qk, counts + b, fctr + kXcds * k, P, mv.bvh,
                                       opts->n_proposal, opts->n_fine, b < packet_segments, stats,
-                                      opts->march_blocks_per_cu, n, st);
+                                      opts->march_blocks_per_cu, n, LvScratch{}, st);
         else
           s = dispatch_march_mfma(fields[k], qk, counts + b, fctr + kXcds * k, P, mv.bvh, b < packet_segments, stats,
                                   opts->march_blocks_per_cu, n, st);
@@ -988,17 +987,17 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
       MR_HIP(hipGetLastError());
     } else if (field) {
       StageTimer tm(b == 0 ? 3 : 1, st, timed);
+      MarchParams Pb = P;
+      Pb.lv = P.lv && b >= packet_segments;   // per-ray segments
       if (opts->sampler == MR_SAMPLER_PROPOSAL)
-        s = dispatch_march_proposal(field, opts->proposal, qi, counts + b, work + kXcds * b, P, mv.bvh, opts->n_proposal,
-                                    opts->n_fine, b < packet_segments, stats, opts->march_blocks_per_cu, n, st);
+        s = dispatch_march_proposal(field, opts->proposal, qi, counts + b, work + kXcds * b, Pb, mv.bvh,
+                                    opts->n_proposal, opts->n_fine, b < packet_segments, stats,
+                                    opts->march_blocks_per_cu, n, lv_scratch(lv_area, b), st);
       else {
-        if (P.lv && b >= packet_segments) {
-          s = dispatch_march_lv(field, qi, counts + b, work + kXcds * b, P, {lv_pace + kLvPaceInts * b, lv_feat}, stats,
-                                st);
+        if (Pb.lv) {
+          s = dispatch_march_lv(field, qi, counts + b, work + kXcds * b, P, lv_scratch(lv_area, b), stats, st);
           if (s != MR_OK) return s;
         }
-        MarchParams Pb = P;
-        Pb.lv = P.lv && b >= packet_segments;
         s = dispatch_march_mfma(field, qi, counts + b, work + kXcds * b, Pb, mv.bvh, b < packet_segments, stats,
                                 opts->march_blocks_per_cu, n, st);
       }
@@ -1011,7 +1010,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
                          counts + b + 1, mv, S, ro, P.span, tail, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
       MR_HIP(hipGetLastError());
       // no light sample on a ray's last segment
-      const LvScratch light_lv = {lv_pace + kLvPaceInts * (max_bounces + 1 + b), lv_feat};
+      const LvScratch light_lv = lv_scratch(lv_area, max_bounces + 1 + b);
       for (int k = 0; light_medium && b < max_bounces && k < n_fields; ++k) {
         s = dispatch_light_march(fields[k], qi, qo, counts + b, k == 0 ? lwork + b : nullptr, light_delta,
                                  opts->use_occupancy != 0, k + 1 == n_fields, ro.radiance, n, lv_light ? &light_lv : nullptr,

@@ -154,3 +154,25 @@ def test_targets_level_by_level(n, n_samples, bins, half):
     assert torch.equal(lohi, torch.cat([p[0] for p in parts]))
     assert torch.equal(tgt, torch.cat([p[1] for p in parts]))
     assert (lohi[::7] == 0).all() and tgt.isfinite().all()
+
+
+# 32 and fewer intervals take half a wave per ray; 17 and 33 leave ragged tiles
+@pytest.mark.parametrize("n_prop,n_fine,half,phalf,occ", [(32, 32, True, True, True), (32, 17, False, False, False),
+                                                          (20, 33, True, False, False), (64, 64, False, True, True),
+                                                          (1, 1, True, True, False)])
+def test_proposal_march_level_by_level(n_prop, n_fine, half, phalf, occ):
+    sc = sg.mid_scene(width=331, height=257)
+    sc.max_bounces = 3
+    F = M.Field(sg.mid_field(9, 0.5, -1.0), **(dict(table_dtype=M.MR_F16, mlp_dtype=M.MR_BF16) if half else {}))
+    P = M.Field(sg.make_proposal(seed=3, table_amp=0.5), table_dtype=M.MR_F16 if phalf else M.MR_F32)
+    if occ:
+        F.build_occupancy(64, 0.3)
+    G = M.Mesh(sc.mesh)
+    o, d, _ = M.camera_rays(sg.cameras_array(sc.cameras))
+    opts = M.make_opts(sc, sampler=M.MR_SAMPLER_PROPOSAL, proposal=P, n_proposal=n_prop, n_fine=n_fine,
+                       use_occupancy=occ)
+    a = _render(F, G, o, d, sc, opts, lean=False)
+    b = _render(F, G, o, d, sc, opts, lean=True)
+    assert (a[2] > 0).sum() > 8192
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
