@@ -129,6 +129,8 @@ __device__ __forceinline__ void march_fields_ray(const RayQueue& q, int r, const
   const int n_cuts = __popcll(__ballot(cut != INFINITY));
   const int total = k1 - k0 + n_cuts;   // pieces
   float Tseg = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
+  float u[4][4];   // SH product of field u_of: a ray stays in a field for many tiles
+  int u_of = -1;
   for (int mb = 0; mb < total; mb += 16) {
     const int m = mb + j;
     const float a = boundary(m, cut, pos, n_cand, t_a, t_b, k0, delta);
@@ -149,8 +151,8 @@ __device__ __forceinline__ void march_fields_ray(const RayQueue& q, int r, const
       const float px = fx + tm * ex, py = fy + tm * ey, pz = fz + tm * ez;
       if (in && P.use_occupancy && F.occ) in = occ_lookup(F, px, py, pz);
       if (__ballot(in) == 0ull) continue;
-      float u[4][4];
-      sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
+      if (u_of != k) sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
+      u_of = k;
       float fe[LY::NF];
       encode_group<NL, TabT>(F, reinterpret_cast<const TabT*>(J.table[k]), px, py, pz, g, fe);
       float sigma, rgb[3];
@@ -251,6 +253,8 @@ __device__ __forceinline__ void march_fields_packet(const RayQueue& q, int r, bo
   }
   const int n_bnd = 2 * J.n;
   float T = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
+  float u[4][4];   // SH product of field u_of
+  int u_of = -1;
   while (__ballot(alive) != 0ull) {
     float b = a;
     if (alive) {
@@ -278,8 +282,8 @@ __device__ __forceinline__ void march_fields_packet(const RayQueue& q, int r, bo
       const float px = fx + tm * ex, py = fy + tm * ey, pz = fz + tm * ez;
       if (in && P.use_occupancy && F.occ) in = occ_lookup(F, px, py, pz);
       if (__ballot(in) == 0ull) continue;
-      float u[4][4];
-      sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
+      if (u_of != k) sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
+      u_of = k;
       float fe[LY::NF];
       encode_group<NL, TabT>(F, reinterpret_cast<const TabT*>(J.table[k]), px, py, pz, g, fe);
       float sigma, rgb[3];
