@@ -168,10 +168,10 @@ __global__ void k_refit_tris(const float* __restrict__ v, const int4* __restrict
                              float4* __restrict__ tris) {
   for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n_prims; p += gridDim.x * blockDim.x) {
     const int4 q = prim_idx[p];
-    const float4 old0 = tris[3 * p], old1 = tris[3 * p + 1];
+    const float4 old0 = tris[3 * p], old1 = tris[3 * p + 1], old2 = tris[3 * p + 2];
     tris[3 * p] = make_float4(v[3 * q.x], v[3 * q.x + 1], v[3 * q.x + 2], old0.w);
     tris[3 * p + 1] = make_float4(v[3 * q.y], v[3 * q.y + 1], v[3 * q.y + 2], old1.w);
-    tris[3 * p + 2] = make_float4(v[3 * q.z], v[3 * q.z + 1], v[3 * q.z + 2], 0.0f);
+    tris[3 * p + 2] = make_float4(v[3 * q.z], v[3 * q.z + 1], v[3 * q.z + 2], old2.w);
   }
 }
 
@@ -214,12 +214,11 @@ __global__ void k_refit_level(BvhNode* __restrict__ nodes, const float4* __restr
 __global__ __launch_bounds__(kTraceBlock) void k_closest(BvhView B, int64_t n, const float* __restrict__ o,
                                                          const float* __restrict__ d, float tmax,
                                                          float* __restrict__ t_hit, int32_t* __restrict__ tri) {
-  __shared__ int stack[kStack * kTraceBlock];
-  __shared__ float tstack[kStack * kTraceBlock];
+  extern __shared__ int2 stack[];   // bvh_entries(B) x kTraceBlock
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const RayPre r = ray_pre(v3(o[3 * i], o[3 * i + 1], o[3 * i + 2]), v3(d[3 * i], d[3 * i + 1], d[3 * i + 2]));
     float t;
-    const int p = bvh_trace<false>(B, r, tmax, t, stack + threadIdx.x, tstack + threadIdx.x, kTraceBlock);
+    const int p = bvh_closest(B, r, tmax, t, stack + threadIdx.x, kTraceBlock);
     t_hit[i] = p >= 0 ? t : INFINITY;
     tri[i] = p >= 0 ? __float_as_int(B.tris[3 * p].w) : -1;
   }
@@ -327,6 +326,8 @@ extern "C" mr_status mr_mesh_build_bvh(const float* host_vertices, int32_t nv, c
     tris[3 * p + 2] = make_float4(v2[0], v2[1], v2[2], 0.0f);
     pidx[p] = make_int4(f[0], f[1], f[2], id);
   }
+  for (const BuildNode& bn : B.nodes)
+    if (bn.count > 0) tris[3 * (bn.first + bn.count - 1) + 2].w = 1.0f;
   // refit order: node ids grouped by depth, deepest first
   int maxd = 0;
   for (int dd : depth_of) maxd = std::max(maxd, dd);
@@ -394,6 +395,7 @@ extern "C" mr_status mr_mesh_build_bvh(const float* host_vertices, int32_t nv, c
   m->view.bvh.nodes = m->nodes_dev;
   m->view.bvh.tris = m->tris_dev;
   m->view.bvh.n_prims = nf;
+  m->view.bvh.depth = B.max_depth;
   m->view.n_mat = n_materials;
   m->view.emissive = 0;
   for (int i = 0; i < n_materials; ++i) {
@@ -457,8 +459,9 @@ extern "C" mr_status mr_mesh_closest_hit(const mr_mesh* m, int64_t n, const floa
   if (!(t_max > 0.0f)) return fail(MR_ERR_INVALID_ARG, "t_max must be > 0");
   hipStream_t st = (hipStream_t)stream;
   const int blocks = (int)std::min<int64_t>((n + kTraceBlock - 1) / kTraceBlock, 16384);
-  hipLaunchKernelGGL(k_closest, dim3(blocks), dim3(kTraceBlock), 0, st, m->view.bvh, n, origins, dirs, t_max, t_hit,
-                     tri);
+  hipLaunchKernelGGL(k_closest, dim3(blocks), dim3(kTraceBlock),
+                     bvh_entries(m->view.bvh) * kTraceBlock * sizeof(int2), st, m->view.bvh, n, origins, dirs, t_max,
+                     t_hit, tri);
   MR_HIP(hipGetLastError());
   return MR_OK;
 }

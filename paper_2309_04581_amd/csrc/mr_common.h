@@ -14,7 +14,7 @@ namespace mr {
 constexpr int kMaxLevels = 16;
 constexpr int kMaxMaterials = 16;
 constexpr int kMaxLights = 8;
-constexpr int kStack = 48;          // BVH traversal stack depth (tree depth is capped below it)
+constexpr int kStack = 48;          // BVH traversal stack that holds any tree (its depth is capped below it)
 constexpr int kLeafSize = 4;
 constexpr int kTraceBlock = 128;    // threads per block of the traversal kernels
 
@@ -87,9 +87,14 @@ struct Material {
 
 struct BvhView {
   const BvhNode* nodes;
-  const float4* tris;  // 3 per prim in leaf order: (v0, id bits), (v1, material bits), (v2, 0)
+  const float4* tris;  // 3 per prim in leaf order: (v0, id bits), (v1, material bits),
+                       // (v2, 1 at the last prim of a leaf, else 0)
   int n_prims;
+  int depth;           // of the deepest leaf
 };
+
+// A traversal holds at most one pending sibling per inner node of its path.
+inline int bvh_entries(const BvhView& B) { return B.depth > 1 ? B.depth : 1; }
 
 // Emitting triangles for light sampling, in face order: x = cumulative
 // choice probability (the last is 1), y = the triangle's own probability,

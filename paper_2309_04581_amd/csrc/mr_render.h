@@ -56,8 +56,7 @@ __device__ __forceinline__ float sample_shadow_world(const BvhView& B, const Mar
       const float sx = P.light_pos[li][0] - px, sy = P.light_pos[li][1] - py, sz = P.light_pos[li][2] - pz;
       const float dist = sqrtf(sx * sx + sy * sy + sz * sz);
       const RayPre sr = ray_pre(v3(px, py, pz), v3(sx / dist, sy / dist, sz / dist));
-      float th;
-      if (bvh_trace<true>(B, sr, dist, th, stack, nullptr, 16) >= 0) m *= P.shadow_mask;
+      if (bvh_any(B, sr, dist, stack, 16)) m *= P.shadow_mask;
     }
   }
   return __shfl(m, lane & 15, 64);
@@ -135,9 +134,9 @@ int device_cus();
 
 // Blocks of a persistent grid of `kernel` (blocks of `threads`): `per_cu`
 // per compute unit, or, for per_cu = 0, as many as are resident at once by
-// the occupancy calculator (queried once per kernel); at least kXcds and at
-// most `cap`.
-int persistent_blocks(const void* kernel, int threads, int per_cu, int64_t cap);
+// the occupancy calculator (queried once per kernel and size `lds` of its
+// dynamic LDS); at least kXcds and at most `cap`.
+int persistent_blocks(const void* kernel, int threads, int per_cu, int64_t cap, size_t lds = 0);
 
 // matrix-core march (march_mfma.hip)
 // packets: 16 consecutive queue rays per wave in step (else one ray per wave);

@@ -14,7 +14,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
-#include <unordered_map>
+#include <map>
 #include <vector>
 
 #include "mr_device.h"
@@ -131,26 +131,31 @@ __global__ void k_init(int64_t n, const float* __restrict__ o, const float* __re
 // ---------------------------------------------------------------------------
 // closest hit of every live ray
 // ---------------------------------------------------------------------------
+// A block's first tile of a queue is the one of its number, so that the
+// blocks that a short or empty queue has no tile for leave without touching
+// the queue's one counter (shading the cloth at 801x603, with as many blocks
+// as the small stacks let in, took 0.44 ms with every tile from the counter and
+// 0.24 so; 0.29 with stacks of 48 entries); its next ones come from the counter.
+__device__ __forceinline__ int next_tile(int* work, int tile, int& s_base) {
+  __syncthreads();
+  if (threadIdx.x == 0) s_base = gridDim.x * tile + atomicAdd(work, tile);
+  __syncthreads();
+  return s_base;
+}
+
 __global__ __launch_bounds__(kTraceBlock) void k_trace(RayQueue q, const int* __restrict__ count, int* __restrict__ work,
                                                        int tile, BvhView B, float t_far, float span,
                                                        int32_t* __restrict__ hit_ids, int hit_stride) {
-  __shared__ int stack[kStack * kTraceBlock];
-  __shared__ float tstack[kStack * kTraceBlock];
+  extern __shared__ int2 stack[];   // bvh_entries(B) x kTraceBlock
   __shared__ int s_base;
   const int cnt = *count;
-  while (true) {
-    if (threadIdx.x == 0) s_base = atomicAdd(work, tile);
-    __syncthreads();
-    const int base = s_base;
-    __syncthreads();
-    if (base >= cnt) break;
+  for (int base = blockIdx.x * tile; base < cnt; base = next_tile(work, tile, s_base)) {
     const int end = min(base + tile, cnt);
     for (int i = base + threadIdx.x; i < end; i += blockDim.x) {
       const int seg = q.depth[i] & 0xFFFF;
       const RayPre r = ray_pre(v3(q.ox[i], q.oy[i], q.oz[i]), v3(q.dx[i], q.dy[i], q.dz[i]));
       float t = INFINITY;
-      const int p = B.n_prims ? bvh_trace<false>(B, r, seg == 0 ? t_far : span, t, stack + threadIdx.x,
-                                                            tstack + threadIdx.x, kTraceBlock) : -1;
+      const int p = bvh_closest(B, r, seg == 0 ? t_far : span, t, stack + threadIdx.x, kTraceBlock);
       q.hit_t[i] = p >= 0 ? t : INFINITY;
       q.hit_p[i] = p;
       if (hit_ids && seg < hit_stride)
@@ -196,18 +201,12 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
                                                        int* __restrict__ count_out, MeshView M, ShadeParams S,
                                                        RenderOut out, float span, int tail, int32_t* __restrict__ hit_ids,
                                                        int hit_stride, unsigned long long* __restrict__ stats) {
-  __shared__ int stack[kStack * kTraceBlock];
-  __shared__ float tstack[kStack * kTraceBlock];
+  extern __shared__ int2 stack[];   // bvh_entries(M.bvh) x kTraceBlock
   __shared__ int s_base;
   const int cnt = *count_in;
   const int lane = threadIdx.x & 63;
   unsigned long long n_seg = 0, n_shadow = 0, n_scat = 0;
-  while (true) {
-  if (threadIdx.x == 0) s_base = atomicAdd(work, tile);
-  __syncthreads();
-  const int tbase = s_base;
-  __syncthreads();
-  if (tbase >= cnt) break;
+  for (int tbase = blockIdx.x * tile; tbase < cnt; tbase = next_tile(work, tile, s_base)) {
   const int tend = min(tbase + tile, cnt);
   for (int i0 = tbase; i0 < tend; i0 += blockDim.x) {
     const int i = i0 + threadIdx.x;
@@ -258,9 +257,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
             const float sdist = sqrtf(dot(sd, sd));
             sd = v3(sd.x / sdist, sd.y / sdist, sd.z / sdist);
             const RayPre sr = ray_pre(so, sd);
-            float th;
             ++n_shadow;
-            if (bvh_trace<true>(M.bvh, sr, sdist, th, stack + threadIdx.x, nullptr, kTraceBlock) >= 0) continue;
+            if (bvh_any(M.bvh, sr, sdist, &stack[threadIdx.x].x, 2 * kTraceBlock)) continue;
             const float g = cosl / d2 * (1.0f / 3.14159265358979323846f);
             lr += tr * mat.albedo[0] * S.lights[li][3] * g;
             lg += tg * mat.albedo[1] * S.lights[li][4] * g;
@@ -294,9 +292,8 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
               const float sdist = sqrtf(dot(sd, sd));
               sd = v3(sd.x / sdist, sd.y / sdist, sd.z / sdist);
               const RayPre sr = ray_pre(so, sd);
-              float th;
               ++n_shadow;
-              if (bvh_trace<true>(M.bvh, sr, (1.0f - 1e-3f) * sdist, th, stack + threadIdx.x, nullptr, kTraceBlock) < 0) {
+              if (!bvh_any(M.bvh, sr, (1.0f - 1e-3f) * sdist, &stack[threadIdx.x].x, 2 * kTraceBlock)) {
                 const Material& em = M.mat[__float_as_int(a1.w)];
                 const float g = cos_p * cos_x / d2 * (0.5f * a2x) / e.y * (1.0f / 3.14159265358979323846f);
                 const float cr = tr * mat.albedo[0] * em.emission[0] * g, cg = tg * mat.albedo[1] * em.emission[1] * g,
@@ -406,7 +403,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade(RayQueue qi, const int* _
       if (cnt > tail) {
         const RayPre nr = ray_pre(v3(nox, noy, noz), v3(ndx, ndy, ndz));
         float th = INFINITY;
-        const int hp = bvh_trace<false>(M.bvh, nr, span, th, stack + threadIdx.x, tstack + threadIdx.x, kTraceBlock);
+        const int hp = bvh_closest(M.bvh, nr, span, th, stack + threadIdx.x, kTraceBlock);
         qo.hit_t[slot] = hp >= 0 ? th : INFINITY;
         qo.hit_p[slot] = hp;
         const int nseg = ndepth & 0xFFFF;
@@ -455,8 +452,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_trace_wide(RayQueue q, cons
                                                                int hit_stride) {
   __shared__ int s_node[kWideWaves][2][kWideFront];
   __shared__ float s_tin[kWideWaves][2][kWideFront];
-  __shared__ int s_stack[kWideWaves][kStack];
-  __shared__ float s_tstack[kWideWaves][kStack];
+  __shared__ int2 s_stack[kWideWaves][kStack];
   if (*gate_count > kTailRays) return;   // the shade pass traced this queue itself
   const int cnt = *count;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -550,7 +546,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_trace_wide(RayQueue q, cons
     if (overflow) {
       if (lane == 0) {
         float th = tmax;
-        pb = bvh_trace<false>(B, R, tmax, th, &s_stack[w][0], &s_tstack[w][0], 1);
+        pb = bvh_closest(B, R, tmax, th, s_stack[w], 1);
         tb = th;
       }
       pb = __shfl(pb, 0, 64);
@@ -697,16 +693,16 @@ int device_cus() {
   return cus;
 }
 
-int persistent_blocks(const void* kernel, int threads, int per_cu, int64_t cap) {
+int persistent_blocks(const void* kernel, int threads, int per_cu, int64_t cap, size_t lds) {
   if (per_cu <= 0) {
     static std::mutex mu;
-    static std::unordered_map<const void*, int> fit;
+    static std::map<std::pair<const void*, size_t>, int> fit;
     std::lock_guard<std::mutex> lock(mu);
-    auto it = fit.find(kernel);
+    auto it = fit.find({kernel, lds});
     if (it == fit.end()) {
       int b = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, threads, 0) != hipSuccess || b <= 0) b = 2;
-      it = fit.emplace(kernel, b).first;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, threads, lds) != hipSuccess || b <= 0) b = 2;
+      it = fit.emplace(std::make_pair(kernel, lds), b).first;
     }
     per_cu = it->second;
   }
@@ -939,10 +935,11 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
 
   const int tile = opts->stage_tile > 0 ? opts->stage_tile : 128;
   const int64_t tiles = (n + tile - 1) / tile;
-  const int trace_blocks =
-      persistent_blocks(reinterpret_cast<const void*>(k_trace), kTraceBlock, opts->stage_blocks_per_cu, tiles);
-  const int shade_blocks =
-      persistent_blocks(reinterpret_cast<const void*>(k_shade<false>), kTraceBlock, opts->stage_blocks_per_cu, tiles);
+  const size_t stack_bytes = bvh_entries(mv.bvh) * kTraceBlock * sizeof(int2);
+  const int trace_blocks = persistent_blocks(reinterpret_cast<const void*>(k_trace), kTraceBlock,
+                                             opts->stage_blocks_per_cu, tiles, stack_bytes);
+  const int shade_blocks = persistent_blocks(reinterpret_cast<const void*>(k_shade<false>), kTraceBlock,
+                                             opts->stage_blocks_per_cu, tiles, stack_bytes);
   const int packet_segments = opts->march_packets == 0 ? 1 : std::max(0, opts->march_packets);
   const int tail = mv.bvh.n_prims > kWideMinPrims ? kTailRays : 0;
   const int wide_blocks = (int)std::max<int64_t>(
@@ -953,8 +950,8 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
     if (b == 0) {
       // later segments are traced by the shade pass that spawns them
       StageTimer tm(0, st, timed);
-      hipLaunchKernelGGL(k_trace, dim3(trace_blocks), dim3(kTraceBlock), 0, st, qi, counts + b, twork + b, tile, mv.bvh,
-                         opts->t_far, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0);
+      hipLaunchKernelGGL(k_trace, dim3(trace_blocks), dim3(kTraceBlock), stack_bytes, st, qi, counts + b, twork + b, tile,
+                         mv.bvh, opts->t_far, P.span, out->hit_ids, out->hit_ids ? out->hit_stride : 0);
       MR_HIP(hipGetLastError());
     }
     if (n_fields > 1 && joint) {
@@ -1006,7 +1003,7 @@ mr_status render_impl(const mr_field* const* fields, const mr_field* const* prop
     {
       StageTimer tm(2, st, timed);
       auto* k = light_medium ? k_shade<true> : k_shade<false>;
-      hipLaunchKernelGGL(k, dim3(shade_blocks), dim3(kTraceBlock), 0, st, qi, counts + b, swork + b, tile, qo,
+      hipLaunchKernelGGL(k, dim3(shade_blocks), dim3(kTraceBlock), stack_bytes, st, qi, counts + b, swork + b, tile, qo,
                          counts + b + 1, mv, S, ro, P.span, tail, out->hit_ids, out->hit_ids ? out->hit_stride : 0, stats);
       MR_HIP(hipGetLastError());
       // no light sample on a ray's last segment
