@@ -37,8 +37,8 @@ PROPOSAL_MACS = 10 * 16 + 16 * 1        # proposal MLP 10 -> 16 -> 1 per proposa
 # taken with rocprofv3 counters is reported only while they are unchanged since
 # the counters were taken.  (The public header only declares the C ABI; the
 # march takes nothing from it but enum constants.)
-MARCH_SOURCES = ["march_mfma.hip", "mr_mfma.h", "mr_field_kernels.h", "mr_device.h", "mr_render.h",
-                 "mr_common.h"]
+MARCH_SOURCES = ["march_mfma.hip", "march_lv.hip", "mr_levels.h", "mr_march.h", "mr_mfma.h",
+                 "mr_field_kernels.h", "mr_device.h", "mr_render.h", "mr_common.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_march_mid_fabric_traffic.md")
 
 
@@ -960,7 +960,7 @@ def main():
     segments = int(counters[1])
 
     # dominant kernel: the march (field gathers + MLPs + compositing)
-    # the march: stage 3 the camera segment (k_march_pc), stage 1 the later segments (k_march_mfma)
+    # the march: stage 3 the camera segment (k_march_pc), stage 1 the later segments (k_march_lv, k_march_mfma)
     march_ms_per_step = (stage_ms[1] + stage_ms[3]) / args.steps
     march_launch_ms = (stage_ms[1] + stage_ms[3]) / max(1, stage_n[1] + stage_n[3])
     launches_per_step = (stage_n[1] + stage_n[3]) / args.steps
@@ -968,7 +968,7 @@ def main():
     tflops = flops_per_step / (march_ms_per_step / 1e3) / 1e12
     bf16_tflops = 6 * 2.0 * split_macs(sc.field) * samples / (march_ms_per_step / 1e3) / 1e12
     gbs = gather_bytes(sc.field) * samples / (march_ms_per_step / 1e3) / 1e9
-    # split: camera segment (k_march_pc) and bounce segments (k_march_mfma); samples of the
+    # split: camera segment (k_march_pc) and bounce segments (k_march_lv, k_march_mfma); samples of the
     # camera segment from the same render stopped at its first surface (the same samples)
     R0 = M.Renderer(n, 0, with_hits=False)
     M.mr_rays_from_cameras(cams, o, d, None, n)
@@ -1030,7 +1030,7 @@ def main():
         # the march's bound: the memory side serving the hash gathers (the 64 MiB
         # table sits in the Infinity Cache in front of HBM); achieved = the
         # algorithmic gather bytes (16 levels x 8 corners x 2 FP32) per second
-        "roofline": {"kernel": "k_march_pc (camera segment) + k_march_mfma (later segments)", "bound": "hbm",
+        "roofline": {"kernel": "k_march_pc (camera segment) + k_march_lv and k_march_mfma (later segments)", "bound": "hbm",
                      "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(),
                      "traffic_unit": "bytes per launch (L2-to-memory reads by request size + writes)",
@@ -1047,7 +1047,7 @@ def main():
                          "frac_of_bf16_mfma_peak": round(bf16_tflops / BF16_MFMA_PEAK_TFLOPS, 4)},
                      "camera_segment": dict(kernel="k_march_pc", **seg_roof(
                          cam_ms, cam_samples, measured_traffic("camera_segment_fabric_bytes"))),
-                     "bounce_segments": dict(kernel="k_march_mfma", **seg_roof(
+                     "bounce_segments": dict(kernel="k_march_lv, k_march_mfma", **seg_roof(
                          bnc_ms, bnc_samples, measured_traffic("bounce_segments_fabric_bytes")))},
         "gather": {"achieved": round(gbs, 1), "unit": "GB/s", "peak_hbm": HBM_PEAK_GBS,
                    "bytes_per_sample": gather_bytes(sc.field)},

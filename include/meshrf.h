@@ -119,7 +119,7 @@ mr_status mr_mlp_fragments(const mr_field_desc* desc, const float* host_mlp, int
  * x, dirs: (n, 3) in world coordinates (mapped into the field's frame when it
  * has a pose); sigma: (n); rgb: (n, 3) or NULL; feat: (n, n_levels*feats)
  * or NULL (interpolated hash features, FP32); raw: (n, density_out) or NULL.
- * Large queries of a 16-level field take 256 MiB of stream-ordered scratch
+ * Large queries of a 16-level field take about 264 MiB of stream-ordered scratch
  * (hipMallocFromPoolAsync) from a pool that keeps one such block per device
  * until the last field is destroyed; under capture or without that memory
  * they are evaluated without it, with the same results. */
@@ -281,7 +281,7 @@ typedef struct {
 } mr_render_out;
 
 /* Bytes of device workspace for n rays: the ray queues and, for 65 536 rays
- * or more, 256 MiB (at 256 compute units) in which bounce rays through a
+ * or more, about 264 MiB (at 256 compute units) in which bounce rays through a
  * 16-level field are marched one hash level at a time.  mr_render also takes
  * a workspace of the queues alone (4096 + 128 n bytes, n rounded up to 64)
  * and then marches them ray by ray: the same results, more slowly. */
