@@ -129,7 +129,11 @@ __device__ __forceinline__ void march_fields_ray(const RayQueue& q, int r, const
   const int n_cuts = __popcll(__ballot(cut != INFINITY));
   const int total = k1 - k0 + n_cuts;   // pieces
   float Tseg = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
-  float u[4][4];   // SH product of field u_of: a ray stays in a field for many tiles
+  // SH product of field u_of: a ray stays in a field for many tiles.  Kept in
+  // FP32 (three fields, 800x450: 13.13 -> 12.95 ms); the BF16 instances have no
+  // registers to keep it in (two / three fields, 500x400: 6.18 / 7.16 ms
+  // without, 6.40 / 7.37 with) and compute it for every tile.
+  float u[4][4];
   int u_of = -1;
   for (int mb = 0; mb < total; mb += 16) {
     const int m = mb + j;
@@ -151,7 +155,7 @@ __device__ __forceinline__ void march_fields_ray(const RayQueue& q, int r, const
       const float px = fx + tm * ex, py = fy + tm * ey, pz = fz + tm * ez;
       if (in && P.use_occupancy && F.occ) in = occ_lookup(F, px, py, pz);
       if (__ballot(in) == 0ull) continue;
-      if (u_of != k) sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
+      if (BF || u_of != k) sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
       u_of = k;
       float fe[LY::NF];
       encode_group<NL, TabT>(F, reinterpret_cast<const TabT*>(J.table[k]), px, py, pz, g, fe);
@@ -282,7 +286,7 @@ __device__ __forceinline__ void march_fields_packet(const RayQueue& q, int r, bo
       const float px = fx + tm * ex, py = fy + tm * ey, pz = fz + tm * ez;
       if (in && P.use_occupancy && F.occ) in = occ_lookup(F, px, py, pz);
       if (__ballot(in) == 0ull) continue;
-      if (u_of != k) sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
+      if (BF || u_of != k) sh_rows<NL, SH, CL, BF>(J.frags[k], ex, ey, ez, lane, u);
       u_of = k;
       float fe[LY::NF];
       encode_group<NL, TabT>(F, reinterpret_cast<const TabT*>(J.table[k]), px, py, pz, g, fe);
