@@ -92,14 +92,14 @@ __device__ __forceinline__ void probe_point(const FieldView& F, int res, int64_t
 constexpr int kOccThreads = 512;
 
 template <int NL, typename TabT, bool SHARED>
-__global__ __launch_bounds__(kOccThreads) void k_occupancy(FieldView F, const TabT* __restrict__ table,
-                                                           const uint32_t* __restrict__ frags, int res, float thresh,
-                                                           uint32_t* __restrict__ words, uint8_t* __restrict__ bytes) {
+__global__ __launch_bounds__(kOccThreads) void k_occupancy(FieldView F, const TabT* __restrict__ table, int res,
+                                                           float thresh, uint32_t* __restrict__ words,
+                                                           uint8_t* __restrict__ bytes) {
   using LY = FragLayout<NL, 4, 1, false>;   // the density layers come first and are the same for every layout
   __shared__ __align__(16) uint32_t sW[LY::C1];
   __shared__ float s_a[2 * NL];
   __shared__ uint32_t s_run[8];
-  for (int i = threadIdx.x; i < LY::C1; i += blockDim.x) sW[i] = frags[i];
+  stage_density<NL>(F.mlp, sW);
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   if (threadIdx.x < 2 * NL) {   // a_i
     float a = 0.0f;
@@ -191,7 +191,7 @@ mr_status launch_occ(mr_field* f, int res, float thresh, uint8_t* bytes, hipStre
   auto* k = shared ? k_occupancy<NL, TabT, true> : k_occupancy<NL, TabT, false>;
   const int blocks = (int)std::min<int64_t>(shared ? groups : (groups + 7) / 8, 2048);
   hipLaunchKernelGGL(k, dim3(blocks), dim3(kOccThreads), 0, st, f->view, reinterpret_cast<const TabT*>(f->table_dev),
-                     f->frag_f32_dev, res, thresh, f->occ_dev, bytes);
+                     res, thresh, f->occ_dev, bytes);
   MR_HIP(hipGetLastError());
   return MR_OK;
 }

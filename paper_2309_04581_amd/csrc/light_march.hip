@@ -69,7 +69,7 @@ __device__ __forceinline__ bool light_long(const LightSeg& S) { return S.k1 - S.
 template <typename TabT>
 __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_light_lv(
     RayQueue q, RayQueue next, const int* __restrict__ count, int* __restrict__ work, FieldView F,
-    const TabT* __restrict__ table, const uint32_t* __restrict__ frags, float delta, int use_occ,
+    const TabT* __restrict__ table, float delta, int use_occ,
     float* __restrict__ radiance, double* __restrict__ scratch, int* __restrict__ pace) {
   constexpr int NL = 16;
   using LY = FragLayout<NL, 4, 1, false>;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
   __shared__ LvBatch B;
   const int cnt = *count;
   if (cnt < kLvMinRays) return;
-  for (int i = threadIdx.x; i < LY::C1; i += kLvThreads) sW[i] = frags[i];
+  stage_density<NL>(F.mlp, sW);
   const int lane = threadIdx.x & 63, j = lane & 15;
   double* my = scratch + (int64_t)blockIdx.x * kLvSamples * NL;
   LvPace pc(pace);
@@ -129,11 +129,11 @@ constexpr int kLightGrab = 16;   // slots a wave takes at a time
 template <int NL, typename TabT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_light_march(
     RayQueue q, RayQueue next, const int* __restrict__ count, int* __restrict__ work, FieldView F,
-    const TabT* __restrict__ table, const uint32_t* __restrict__ frags, float delta, int use_occ, int last, int lv,
+    const TabT* __restrict__ table, float delta, int use_occ, int last, int lv,
     float* __restrict__ radiance) {
   using LY = FragLayout<NL, 4, 1, false>;   // the density layers come first and are the same for every layout
   __shared__ __align__(16) uint32_t sW[LY::C1];
-  for (int i = threadIdx.x; i < LY::C1; i += blockDim.x) sW[i] = frags[i];
+  stage_density<NL>(F.mlp, sW);
   __syncthreads();
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   const int cnt = *count, waves = gridDim.x * 4;
@@ -193,14 +193,14 @@ mr_status launch_light(const mr_field* f, RayQueue q, RayQueue next, const int* 
   if constexpr (NL == 16)
     if (lv) {
       hipLaunchKernelGGL(k_light_lv<TabT>, dim3(lv_blocks()), dim3(kLvThreads), 0, st, q, next, count, work, f->view, tab,
-                         f->frag_f32_dev, delta, use_occ, radiance, lv->feat, lv->pace);
+                         delta, use_occ, radiance, lv->feat, lv->pace);
       MR_HIP(hipGetLastError());
     }
   // its queue head is its own: the counter after k_light_lv's
   if (work && lv) work += kMaxBounces + 2;
   auto* k = k_light_march<NL, TabT>;
   const int blocks = persistent_blocks(reinterpret_cast<const void*>(k), 256, 0, (n + 63) / 64);
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, next, count, work, f->view, tab, f->frag_f32_dev,
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, next, count, work, f->view, tab,
                      delta, use_occ, last ? 1 : 0, lv ? 1 : 0, radiance);
   MR_HIP(hipGetLastError());
   return MR_OK;

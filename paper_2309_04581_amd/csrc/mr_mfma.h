@@ -158,6 +158,34 @@ __device__ __forceinline__ f4v mma6(const V& w0, const V& w1, const V& w2, const
   return mma(w0, x0, acc);
 }
 
+// The density layers' FP32 fragments (words 0 .. C1 - 1 of the host's layout)
+// from the field's flat weights, by the whole block.  For kernels that follow
+// the weights as they are when they run: mr_field_params hands out their
+// address, and the fragments laid out when the field was created do not see
+// what a caller writes there.
+template <int NL>
+__device__ __forceinline__ void stage_density(const float* __restrict__ mlp, uint32_t* __restrict__ W) {
+  using LY = FragLayout<NL, 4, 1, false>;   // the density layers come first and are the same for every layout
+  auto put = [&](uint32_t* w, int psize, float a, float b) {
+    const uint32_t p0 = pack2_bf16(a, b);
+    const float ra = a - __uint_as_float(p0 << 16), rb = b - __uint_as_float(p0 & 0xFFFF0000u);
+    const uint32_t p1 = pack2_bf16(ra, rb);
+    w[0] = p0;
+    w[psize] = p1;
+    w[2 * psize] = pack2_bf16(ra - __uint_as_float(p1 << 16), rb - __uint_as_float(p1 & 0xFFFF0000u));
+  };
+  for (int i = threadIdx.x; i < LY::P1; i += blockDim.x) {   // [64][32]
+    const int e = 2 * (i % LY::W1), lane = i / LY::W1 % 64, s = i / LY::W1 / 64, ks = s % LY::KS1;
+    const float* m = mlp + (s / LY::KS1 * 16 + lane % 16) * 32;
+    put(W + LY::L1 + i, LY::P1, m[frag_k(0, LY::NF, ks, lane / 16, e)], m[frag_k(0, LY::NF, ks, lane / 16, e + 1)]);
+  }
+  for (int i = threadIdx.x; i < LY::P2; i += blockDim.x) {   // [16][64]
+    const int e = 2 * (i % LY::W2), lane = i / LY::W2 % 64, ks = i / LY::W2 / 64;
+    const float* m = mlp + 2048 + lane % 16 * 64;
+    put(W + LY::L2 + i, LY::P2, m[frag_k(1, LY::NF, ks, lane / 16, e)], m[frag_k(1, LY::NF, ks, lane / 16, e + 1)]);
+  }
+}
+
 // ReLU on the bit pattern: positive floats order like positive integers and
 // every value with the sign bit set becomes +0, so max_i32(bits, 0) is max(x,
 // 0) in one instruction (fmaxf on a matrix-core result first quiets a
