@@ -621,7 +621,8 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
   int cur = 0, end = 0;
   while (true) {
     if (threadIdx.x < 64)
-      B.take(work, n, grab, cur, end, [&](int r, RaySeg& S) {
+      B.take(work, n, grab, cur, end, [&](int ray, RaySeg& S) {
+        const int64_t r = ray;   // 3 r passes 2^31 where n passes 715 827 882
         S.ox = o[3 * r]; S.oy = o[3 * r + 1]; S.oz = o[3 * r + 2];
         S.dx = d[3 * r]; S.dy = d[3 * r + 1]; S.dz = d[3 * r + 2];
         S.t_a = t_near;
@@ -635,7 +636,7 @@ __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4)))
         lohi[2 * r] = hit ? S.lo : 0.0f;
         lohi[2 * r + 1] = hit ? S.hi : 0.0f;
         if (!hit) {
-          for (int b = 0; b < n_bins; ++b) target[(int64_t)r * n_bins + b] = 0.0f;
+          for (int b = 0; b < n_bins; ++b) target[r * n_bins + b] = 0.0f;
           return false;
         }
         S.k0 = max(0, (int)floorf((S.lo - t_near) / delta) - 1);
