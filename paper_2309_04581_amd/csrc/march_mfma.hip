@@ -14,6 +14,7 @@
 //              carried from tile to tile; better for incoherent bounce rays
 //              and for short queues, where one ray's samples would otherwise
 //              be walked one at a time.
+#include <climits>
 #include <cstring>
 #include <vector>
 
@@ -249,11 +250,12 @@ __device__ __forceinline__ void march_packet(const RayQueue& q, const PacketRay&
 // PK: 16-ray packets (march_packet), else one ray per wave (march_ray).
 // SHADOW: the shadow mask per field sample (instances without it carry none
 // of its code or registers).
-// At most this many rays per block: the per-ray march splits each ray over
-// the four waves of a block instead of taking one ray per wave.
+// At most this many rays per resident block (MarchParams::resident): the
+// per-ray march splits each ray over the four waves of a block instead of
+// taking one ray per wave.
 constexpr int kSplitRaysPerBlock = 8;
-// Up to this many packets per two blocks, each packet is split over a block's
-// four waves.  A packet walks its steps one after the other (1.4 us each on
+// Up to this many packets per two resident blocks, each packet is split over a
+// block's four waves.  A packet walks its steps one after the other (1.4 us each on
 // the 8-level layout, 4 on the 16-level one), so with fewer packets than
 // waves a launch lasts as long as one packet: the camera march of a 64x64 tiny
 // frame took 87 us, 31 split.  One-bounce frames of 4 096 / 9 216 / 16 384 /
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   unsigned long long nsamp = 0;
   bool cnt_done = false;   // the short-queue path marched every ray
   if constexpr (!PK && !SHADOW) {
-    if (cnt <= kSplitRaysPerBlock * (int)gridDim.x) {
+    if (cnt <= kSplitRaysPerBlock * P.resident) {
       __shared__ float part[4][4];
       for (int r = blockIdx.x; r < cnt; r += gridDim.x)
         march_ray_split<NL, SH, CL, TabT, BF>(q, r, F, table, sW, P, B, use_occ, lane, threadIdx.x >> 6, part, nsamp);
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
           march_ray<NL, SH, CL, TabT, BF, SHADOW>(q, r, F, table, sW, P, B, stack, use_occ, lane, nsamp);
         }
     }
-  } else if (cnt <= 8 * split_packets_per_two_blocks<NL>() * (int)gridDim.x) {
+  } else if (cnt <= 8 * split_packets_per_two_blocks<NL>() * P.resident) {
     __shared__ __align__(16) float part[4][16][4];
     for (int base = 16 * blockIdx.x; base < cnt; base += 16 * gridDim.x) {
       const PacketRay R = packet_ray(q, base + j, cnt, F);
@@ -567,13 +569,15 @@ mr_status launch_march_mode(const mr_field* f, RayQueue q, const int* count, int
   auto* k = k_march_mfma<NL, SH, CL, TabT, BF, PK, SHADOW>;
   const int64_t cap = PK ? (n + 15) / 16 : (n + 3) / 4;
   const int blocks = persistent_blocks(reinterpret_cast<const void*>(k), 256, blocks_per_cu, cap);
+  MarchParams Ps = P;
+  Ps.resident = persistent_blocks(reinterpret_cast<const void*>(k), 256, 0, INT_MAX);
   // producer and consumer waves pay for the 16-level layout; with 8 levels a
   // producer's gather is too short to hide behind a consumer's tile (the cloth
   // workload ran 6.24 ms per frame with them against 5.56 ms without).  Few
   // packets are split over a block's waves instead (above),
   // unless the caller bounds the waits, which only the former have.
   if constexpr (PK && !SHADOW && NL == 16) {
-    if (n > 8 * split_packets_per_two_blocks<NL>() * (int64_t)blocks || P.wait_polls > 0) {
+    if (n > 8 * split_packets_per_two_blocks<NL>() * (int64_t)Ps.resident || P.wait_polls > 0) {
       auto* kp = k_march_pc<NL, SH, CL, TabT, BF>;
       const int pairs = persistent_blocks(reinterpret_cast<const void*>(kp), kPcThreads, blocks_per_cu,
                                           (n + 16 * kPcPairs - 1) / (16 * kPcPairs));
@@ -584,7 +588,7 @@ mr_status launch_march_mode(const mr_field* f, RayQueue q, const int* count, int
       return MR_OK;
     }
   }
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, count, work, f->view, tab, fr, P, B, stats);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, q, count, work, f->view, tab, fr, Ps, B, stats);
   MR_HIP(hipGetLastError());
   return MR_OK;
 }

@@ -40,6 +40,10 @@ struct MarchParams {
   int wait_polls;
   int* gave_up;
   int lv;             // queues of kLvMinRays or more are marched level by level
+  // blocks of the march kernel that are resident at once: what the splits of
+  // short queues are chosen by, whatever grid the caller's launch shape gives
+  // (a split rounds differently, and results do not depend on that shape)
+  int resident;
 };
 
 // Shadow mask of the sample of column j (Sec. 3.1 "Shadow rays"): a lane of
