@@ -1275,7 +1275,7 @@ extern "C" mr_status mr_render_graph_create(const mr_field* field, const mr_mesh
   if (g_prof.on) return fail(MR_ERR_STATE, "kernel timing is on; disable it before capturing");
   mr_status s = validate_render(field, mesh, n, origins, dirs, max_bounces, host_lights, n_lights, opts, out);
   if (s != MR_OK) return s;
-  if (!workspace || workspace_bytes < mr_render_workspace_size(n))
+  if (!workspace || workspace_bytes < queues_bytes(n, 1))
     return fail(MR_ERR_INVALID_ARG, "workspace smaller than mr_render_workspace_size(n)");
   hipStream_t st = nullptr;
   MR_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
@@ -1454,7 +1454,7 @@ extern "C" mr_status mr_autotune_search(const mr_field* field, const mr_mesh* me
   if (passes < 1 || passes > 4) return fail(MR_ERR_INVALID_ARG, "passes must be in 1..4");
   mr_status s = validate_render(field, mesh, n, origins, dirs, max_bounces, host_lights, n_lights, opts, out);
   if (s != MR_OK) return s;
-  if (!workspace || workspace_bytes < mr_render_workspace_size(n))
+  if (!workspace || workspace_bytes < queues_bytes(n, 1))
     return fail(MR_ERR_INVALID_ARG, "workspace smaller than mr_render_workspace_size(n)");
   hipStream_t st = (hipStream_t)stream;
   hipEvent_t a = nullptr, b = nullptr;
