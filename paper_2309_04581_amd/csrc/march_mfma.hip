@@ -16,6 +16,7 @@
 //              be walked one at a time.
 #include <climits>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "mr_field_kernels.h"
@@ -515,36 +516,63 @@ __global__ __launch_bounds__(kPcThreads) __attribute__((amdgpu_waves_per_eu(4)))
   }
 }
 
+// Point queries, a tile of 16 points per wave: the small ones, whose time is
+// the latency of one tile, and what query_lv does not take.  The weights are
+// on their way while the first points are, and a wave gathers its first tile
+// before it waits for the block; the tiles after it are code of their own (with
+// one loop for both, 3 M random points of an 8-level FP32 field took 450 us
+// instead of 416).  The BF16 instances are held to 256 registers, so that two
+// waves share a SIMD.  16 levels of 2^19 entries, 4 000 / 16 000 / 48 000 /
+// 90 000 random points, us: FP32 21.3 / 31.7 / 70.3 / 119 with the weights
+// staged first, now 12.3 / 19.8 / 47.2 / 85; FP16 table and BF16 MLPs 13.9 /
+// 20.9 / 57.5 / 110, now 10.9 / 16.2 / 38.5 / 69.
+constexpr int query_waves(bool bf) { return bf ? 2 : 1; }
+
 template <int NL, int SH, int CL, typename TabT, bool BF>
-__global__ __launch_bounds__(256) void k_query_mfma(FieldView F, const TabT* __restrict__ table,
-                                                    const uint32_t* __restrict__ frags, int64_t n,
-                                                    const float* __restrict__ x, const float* __restrict__ dirs,
-                                                    float* __restrict__ sigma_out, float* __restrict__ rgb_out,
-                                                    float* __restrict__ feat_out, float* __restrict__ raw_out) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(query_waves(BF)))) void k_query_mfma(
+    FieldView F, const TabT* __restrict__ table, const uint32_t* __restrict__ frags, int64_t n,
+    const float* __restrict__ x, const float* __restrict__ dirs, float* __restrict__ sigma_out,
+    float* __restrict__ rgb_out, float* __restrict__ feat_out, float* __restrict__ raw_out) {
   using LY = FragLayout<NL, SH, CL, BF>;
   __shared__ __align__(16) uint32_t sW[LY::TOTAL];
-  for (int i = threadIdx.x; i < LY::TOTAL; i += blockDim.x) sW[i] = frags[i];
-  __syncthreads();
+  static_assert(LY::TOTAL % 4 == 0, "the weights are staged 16 bytes at a time");
+  constexpr int kStage = (LY::TOTAL / 4 + 255) / 256;
+  uint4 w[kStage];
+#pragma unroll
+  for (int k = 0; k < kStage; ++k)
+    w[k] = reinterpret_cast<const uint4*>(frags)[min((int)threadIdx.x + 256 * k, LY::TOTAL / 4 - 1)];
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
-  const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  for (int64_t t = wave; t * 16 < n; t += waves) {
+  int64_t t = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+  float px, py, pz, dx, dy, dz, fe[LY::NF];
+  auto points = [&] {   // the tile's points; past the end the last one
+    const int64_t pc = min(t * 16 + j, n - 1);
+    px = x[3 * pc]; py = x[3 * pc + 1]; pz = x[3 * pc + 2];
+    dx = dy = 0.0f;
+    dz = 1.0f;
+    if (dirs) { dx = dirs[3 * pc]; dy = dirs[3 * pc + 1]; dz = dirs[3 * pc + 2]; }
+  };
+  points();
+#pragma unroll
+  for (int k = 0; k < kStage; ++k)
+    if ((int)threadIdx.x + 256 * k < LY::TOTAL / 4) reinterpret_cast<uint4*>(sW)[threadIdx.x + 256 * k] = w[k];
+  to_field_frame(F, px, py, pz, dx, dy, dz);
+  encode_group<NL, TabT>(F, table, px, py, pz, g, fe);
+  __syncthreads();
+  auto tile = [&](auto first) {
     const int64_t p = t * 16 + j;
     const bool valid = p < n;
-    const int64_t pc = valid ? p : n - 1;
-    float px = x[3 * pc], py = x[3 * pc + 1], pz = x[3 * pc + 2];
-    float dx = 0.0f, dy = 0.0f, dz = 1.0f;
-    if (dirs) { dx = dirs[3 * pc]; dy = dirs[3 * pc + 1]; dz = dirs[3 * pc + 2]; }
-    to_field_frame(F, px, py, pz, dx, dy, dz);
+    if constexpr (!decltype(first)::value) {
+      points();
+      to_field_frame(F, px, py, pz, dx, dy, dz);
+    }
     float u[4][4];
     sh_rows<NL, SH, CL, BF>(sW, dx, dy, dz, lane, u);
-    float fe[LY::NF];
-    encode_group<NL, TabT>(F, table, px, py, pz, g, fe);
+    if constexpr (!decltype(first)::value) encode_group<NL, TabT>(F, table, px, py, pz, g, fe);
     float sigma, rgb[3];
     f4v raw;
     mlp_tile<NL, SH, CL, BF>(sW, fe, u, F.density_offset, lane, sigma, rgb, raw);
-    if (!valid) continue;
-    if (g == 0) {
+    if (g == 0 && valid) {
       sigma_out[p] = sigma;
       if (rgb_out) {
         rgb_out[3 * p] = rgb[0];
@@ -552,13 +580,15 @@ __global__ __launch_bounds__(256) void k_query_mfma(FieldView F, const TabT* __r
         rgb_out[3 * p + 2] = rgb[2];
       }
     }
-    if (feat_out)
+    if (feat_out && valid)
 #pragma unroll
       for (int k = 0; k < LY::NF; ++k) feat_out[p * 2 * NL + frag_k(0, LY::NF, 0, g, k)] = fe[k];
-    if (raw_out)
+    if (raw_out && valid)
 #pragma unroll
       for (int v = 0; v < 4; ++v) raw_out[p * 16 + 4 * g + v] = raw[v];
-  }
+  };
+  if (t * 16 < n) tile(std::true_type());
+  for (t += waves; t * 16 < n; t += waves) tile(std::false_type());
 }
 
 template <int NL, int SH, int CL, typename TabT, bool BF, bool PK, bool SHADOW>
