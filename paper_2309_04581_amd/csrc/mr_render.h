@@ -178,11 +178,25 @@ struct LvScratch {
 LvScratch lv_scratch(void* area, int launch);   // of the lv_bytes() at area
 int lv_blocks();
 size_t lv_bytes();
-// Point queries go level by level from this many points: 50 000 / 100 000 / 1 M
-// random points took 107 / 193 / 1 053 us in k_query_mfma and 99 / 128 / 512
-// level by level (FP32), 68 / 121 / 767 and 88 / 109 / 385 (FP16 table, whose
-// levels are half as large).
-inline int64_t lv_min_points(const mr_field* f) { return f->view.table_dtype == MR_F16 ? 98304 : 49152; }
+// Point queries go level by level from this many points, whatever order they
+// come in: points in order share lines in k_query_mfma too, and gain later or
+// not at all.  k_query_mfma / level by level, us, 2^19 entries, random points |
+// a regular grid | 64 points along each of many rays:
+// FP32      131 072: 119 / 140 | 69 / 111 | 81 / 130    196 608: 175 / 164 | 91 / 128 | 118 / 151
+//           524 288: 447 / 308 | 179 / 210 | 309 / 270  3 M: 2574 / 1291 | 639 / 730 | 1767 / 1070
+// FP16,     131 072: 96 / 115 | 43 / 93 | 68 / 112      196 608: 140 / 130 | 54 / 100 | 99 / 126
+// BF16 MLPs 524 288: 372 / 236 | 99 / 160 | 260 / 216   3 M: 2177 / 1037 | 364 / 554 | 1492 / 870
+// The line lies where random points cross (for FP16 tables below 2^19 entries
+// that is later: 2^17, 196 608 / 262 144 points, 95 / 107 and 125 / 127).  A
+// grid there is no slower than it was when k_query_mfma staged its weights
+// before its points (344 / 127 us for 262 144).  With BF16 MLPs of one colour
+// layer it would be (57 us against 90 for 166 375, 311 against 511 for 3 M),
+// and those fields keep to k_query_mfma.
+inline int64_t lv_min_points(const mr_field* f) {
+  const auto& v = f->view;
+  if (v.mlp_dtype == MR_BF16 && v.c_layers == 1) return INT64_MAX;
+  return v.table_dtype == MR_F16 && v.log2_table < 19 ? 262144 : 196608;
+}
 bool lv_field(const mr_field* f);   // a field whose levels fit a die's L2 and whose table does not
 
 // Scratch for a call without a workspace (false under capture or without
