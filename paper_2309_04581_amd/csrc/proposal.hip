@@ -598,10 +598,24 @@ __device__ __forceinline__ float tile_bins(float a, float b, float D, float w, b
 
 // The same one hash level at a time (mr_levels.h): training rays are as
 // incoherent as bounce rays.  Without a segment in the box a ray's range and
-// histogram are zeros.  4 096 / 8 192 / 16 384 / 65 536 rays of 256 intervals
-// took 376 / 720 / 1 418 / 5 611 us in k_prop_targets and 372 / 524 / 887 /
-// 2 860 so; with 64 intervals 4 096 / 16 384 took 160 / 559 and 189 / 397.
-constexpr int64_t kTargetsLvMin = 6144;
+// histogram are zeros.
+//
+// Whatever order the rays come in: those of neighbouring pixels share lines in
+// k_prop_targets too, so the line lies where they cross.  k_prop_targets / level
+// by level, us, 2^19 entries, random rays | camera rays in order:
+// FP32       64 intervals, 12 544 rays 432 / 339 | 241 / 260, 16 384: 566 / 400 | 301 / 297
+//           256 intervals,  6 400 rays 576 / 457 | 299 / 333,  9 216: 816 / 576 | 407 / 413
+// FP16,      64 intervals, 16 384 rays 467 / 341 | 246 / 276, 25 600: 726 / 458 | 360 / 356
+// BF16 MLPs 256 intervals,  6 400 rays 499 / 384 | 261 / 295,  9 216: 696 / 478 | 357 / 362
+// Smaller FP16 tables (2^17: 36 864 rays of 64, 629 / 585 | 388 / 418) and larger
+// FP32 ones (2^20: 16 384 of 256, 1546 / 1132 | 725 / 756) cross later.
+bool targets_lv(const mr_field* f, int64_t n, int n_samples) {
+  const bool fast = f->view.table_dtype == MR_F16 || f->view.mlp_dtype == MR_BF16;
+  const int t = f->view.log2_table;
+  if (n >= (fast ? (t < 19 ? 65536 : 32768) : (t > 19 ? 24576 : 16384))) return true;
+  const bool pair = (f->view.table_dtype == MR_F16) == (f->view.mlp_dtype == MR_BF16);
+  return pair && (fast ? t >= 19 : t == 19) && n >= 6144 && n * n_samples >= 10 << 18;
+}
 
 template <typename TabT, bool BF>
 __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_prop_targets_lv(
@@ -685,8 +699,13 @@ __global__ __launch_bounds__(256) void k_prop_targets(FieldView F, const TabT* _
                                                       float t_near, float t_far, int n_samples, int n_bins,
                                                       float* __restrict__ lohi, float* __restrict__ target) {
   using LY = FragLayout<NL, SH, CL, BF>;
+  // Only the density layers are staged (FP32, 4 096 rays of 64 intervals, random
+  // | camera: all layers 162 | 102 us, so 150 | 92), in an array that would hold
+  // all: with no more LDS than they need, more waves share a compute unit and
+  // evict each other's lines (2^20 entries, 12 544 camera rays of 400 intervals:
+  // 795 us so, 848 with the smaller array).
   __shared__ __align__(16) uint32_t sW[LY::TOTAL];
-  for (int i = threadIdx.x; i < LY::TOTAL; i += blockDim.x) sW[i] = frags[i];
+  for (int i = threadIdx.x; i < LY::C1; i += blockDim.x) sW[i] = frags[i];
   __syncthreads();
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
@@ -704,8 +723,6 @@ __global__ __launch_bounds__(256) void k_prop_targets(FieldView F, const TabT* _
       const float bw = (hi - lo) / (float)n_bins;
       const int k0 = max(0, (int)floorf((lo - t_near) / delta) - 1);
       const int k1 = min(n_samples, (int)ceilf((hi - t_near) / delta) + 1);
-      float u_sh[4][4];
-      sh_rows<NL, SH, CL, BF>(sW, dx, dy, dz, lane, u_sh);
       float Tseg = 1.0f;
       for (int kb = k0; kb < k1; kb += 16) {
         const int k = kb + j;
@@ -716,9 +733,8 @@ __global__ __launch_bounds__(256) void k_prop_targets(FieldView F, const TabT* _
         const float tm = 0.5f * (a + b), D = b - a;
         float fe[LY::NF];
         encode_group<NL, TabT>(F, table, ox + tm * dx, oy + tm * dy, oz + tm * dz, g, fe);
-        float sigma, rgb[3];
-        f4v raw;
-        mlp_tile<NL, SH, CL, BF>(sW, fe, u_sh, F.density_offset, lane, sigma, rgb, raw);
+        const f4v raw = density_raw<NL, SH, CL, BF>(sW, fe, lane);
+        const float sigma = softplusf(__shfl(raw[0], j, 64) + F.density_offset);
         const float alpha = valid ? -expm1f(-sigma * D) : 0.0f;
         const float incl = sc16_mul(1.0f - alpha, j);
         float excl = __shfl_up(incl, 1, 16);
@@ -979,7 +995,7 @@ mr_status launch_targets(const mr_field* f, int64_t n, const float* o, const flo
   const uint32_t* fr = BF ? f->frag_bf16_dev : f->frag_f32_dev;
   if constexpr (NL == 16) {
     LvScratch lv;
-    if (n >= kTargetsLvMin && n < (1 << 30) && lv_field(f) && lv_lease(st, &lv)) {
+    if (n < (1 << 30) && lv_field(f) && targets_lv(f, n, n_samples) && lv_lease(st, &lv)) {
       hipLaunchKernelGGL((k_prop_targets_lv<TabT, BF>), dim3(lv_blocks()), dim3(kLvThreads), 0, st, f->view,
                          reinterpret_cast<const TabT*>(f->table_dev), fr, (int)n, o, d, t_near, t_far, n_samples, n_bins,
                          lohi, target, lv.feat, lv.pace, lv.pace + kLvPaceInts);

@@ -1,0 +1,25 @@
+"""Proposal targets on either side of the sizes from which they go level by
+level: the same bits as the same rays in small calls."""
+import pytest
+import torch
+
+from paper_2309_04581_amd import meshrf as M
+from paper_2309_04581_amd import scenegen as sg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("half,log2_table,n,n_samples", [
+    (False, 19, 16383, 32), (False, 19, 16384, 32), (False, 19, 9215, 256), (False, 19, 9216, 256),
+    (False, 20, 24575, 7), (False, 20, 24576, 7), (True, 19, 32767, 17), (True, 19, 32768, 17), (True, 19, 9216, 256),
+    (True, 17, 65535, 9), (True, 17, 65536, 9)])
+def test_targets_rule(half, log2_table, n, n_samples):
+    f = sg.make_field(n_levels=16, feats=2, log2_table=log2_table, n_min=16, n_max=1024, d_hidden=64, d_out=16,
+                      c_hidden=64, c_layers=2, sh=16, seed=3, table_amp=0.5)
+    F = M.Field(f, **(dict(table_dtype=M.MR_F16, mlp_dtype=M.MR_BF16) if half else {}))
+    T = M.ProposalTrainer(M.Field(sg.make_proposal()), n_bins=20)
+    o, d = (torch.from_numpy(a).cuda() for a in sg.random_rays(n, seed=n))
+    lohi, tgt = T.targets(F, o, d, 0.05, 4.0, n_samples)
+    parts = [T.targets(F, p, q, 0.05, 4.0, n_samples) for p, q in zip(o.split(4000), d.split(4000))]
+    assert torch.equal(lohi, torch.cat([p[0] for p in parts]))
+    assert torch.equal(tgt, torch.cat([p[1] for p in parts]))
