@@ -293,10 +293,14 @@ __device__ __forceinline__ float box_hit(const RayPre& r, float lx, float ly, fl
 // wave) took 241 us with stacks of 48 entries, which left 6 waves to a CU, 149
 // with 24, 122 with 16; stacks are as deep as the tree (13 here), which gives
 // 24 waves.  A lane that reaches a leaf keeps it and walks on until kLeafLanes
-// lanes hold one or none has a node left to visit, and only then are triangles
-// tested (122 -> 100 us): a ray tests 1.5 triangles, but a wave that tests them
-// as each lane gets there runs that code in nearly every step.  4 to 16 lanes
-// measure 99 to 103 us, 24 and more 103 to 107.
+// lanes or half of those still in the loop hold one, or none has a node left to
+// visit, and only then are triangles tested (122 -> 95 us): a ray tests 1.5
+// triangles, but a wave that tests them as each lane gets there runs that code
+// in nearly every step.  4 to 16 lanes measure 99 to 103 us without the half, 24
+// and more 103 to 107.  The half is for waves whose other rays have ended, or
+// never hit a box: 2 025 scattered rays against the 20 494 triangles of a glass
+// sphere, a cube and a floor took 62 us with triangles tested at once, 77 waiting
+// for 12 lanes, 58 so.
 constexpr int kLeafLanes = 12;
 
 __device__ __forceinline__ int bvh_closest(const BvhView& B, const RayPre& r, float tmax, float& t_best, int2* stack,
@@ -335,7 +339,8 @@ __device__ __forceinline__ int bvh_closest(const BvhView& B, const RayPre& r, fl
         }
       }
     }
-    if (__ballot(cur >= 0) == 0 || __popcll(__ballot(leaf != kNone)) >= kLeafLanes) {
+    const int held = __popcll(__ballot(leaf != kNone));
+    if (__ballot(cur >= 0) == 0 || held >= kLeafLanes || 2 * held >= __popcll(__ballot(true))) {
       if (leaf != kNone) {
         float last;
         int p = ~leaf;
