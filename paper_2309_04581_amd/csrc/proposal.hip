@@ -607,12 +607,15 @@ __device__ __forceinline__ float tile_bins(float a, float b, float D, float w, b
 //           256 intervals,  6 400 rays 576 / 457 | 299 / 333,  9 216: 816 / 576 | 407 / 413
 // FP16,      64 intervals, 16 384 rays 467 / 341 | 246 / 276, 25 600: 726 / 458 | 360 / 356
 // BF16 MLPs 256 intervals,  6 400 rays 499 / 384 | 261 / 295,  9 216: 696 / 478 | 357 / 362
-// Smaller FP16 tables (2^17: 36 864 rays of 64, 629 / 585 | 388 / 418) and larger
-// FP32 ones (2^20: 16 384 of 256, 1546 / 1132 | 725 / 756) cross later.
+// Smaller tables (FP16 of 2^17: 36 864 rays of 64, 629 / 585 | 388 / 418; FP32 of
+// 2^16: the same rays 711 / 693 | 418 / 426, 65 536 of them 1229 / 1023 | 808 /
+// 638) and larger FP32 ones (2^20: 16 384 of 256, 1546 / 1132 | 725 / 756) cross
+// later.
 bool targets_lv(const mr_field* f, int64_t n, int n_samples) {
   const bool fast = f->view.table_dtype == MR_F16 || f->view.mlp_dtype == MR_BF16;
   const int t = f->view.log2_table;
-  if (n >= (fast ? (t < 19 ? 65536 : 32768) : (t > 19 ? 24576 : 16384))) return true;
+  const int line = fast ? (t < 19 ? 65536 : 32768) : t > 19 ? 24576 : t > 16 ? 16384 : 65536;
+  if (n >= line) return true;
   const bool pair = (f->view.table_dtype == MR_F16) == (f->view.mlp_dtype == MR_BF16);
   return pair && (fast ? t >= 19 : t == 19) && n >= 6144 && n * n_samples >= 10 << 18;
 }

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("half,log2_table,n,n_samples", [
     (False, 19, 16383, 32), (False, 19, 16384, 32), (False, 19, 9215, 256), (False, 19, 9216, 256),
     (False, 20, 24575, 7), (False, 20, 24576, 7), (True, 19, 32767, 17), (True, 19, 32768, 17), (True, 19, 9216, 256),
-    (True, 17, 65535, 9), (True, 17, 65536, 9)])
+    (True, 17, 65535, 9), (True, 17, 65536, 9), (False, 16, 65535, 9), (False, 16, 65536, 9)])
 def test_targets_rule(half, log2_table, n, n_samples):
     f = sg.make_field(n_levels=16, feats=2, log2_table=log2_table, n_min=16, n_max=1024, d_hidden=64, d_out=16,
                       c_hidden=64, c_layers=2, sh=16, seed=3, table_amp=0.5)
