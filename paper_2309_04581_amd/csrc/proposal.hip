@@ -1009,7 +1009,14 @@ mr_status launch_targets(const mr_field* f, int64_t n, const float* o, const flo
     }
   }
   const int blocks = (int)std::min<int64_t>((n + 3) / 4, (int64_t)device_cus() * 8);
-  hipLaunchKernelGGL((k_prop_targets<NL, SH, CL, TabT, BF>), dim3(blocks), dim3(256), 0, st, f->view,
+  // With FP16 tables and BF16 MLPs four blocks would share a compute unit, whose
+  // gathers evict each other's lines where the table is larger than the L2s
+  // together: unused LDS keeps it at two (2^19 entries, 9 216 rays of 256
+  // intervals, random | camera 806 | 367 us with four, 778 | 323 with two; 2^20
+  // 900 | 408, 864 | 359; 2^18 645 | 308, 630 | 281; 2^17 the other way, 16 384
+  // camera rays of 64: 196 with four, 211 with two).
+  const size_t unused = NL == 16 && BF && sizeof(TabT) == 2 && f->view.log2_table >= 18 ? 40960 : 0;
+  hipLaunchKernelGGL((k_prop_targets<NL, SH, CL, TabT, BF>), dim3(blocks), dim3(256), unused, st, f->view,
                      reinterpret_cast<const TabT*>(f->table_dev), fr, n, o, d, t_near, t_far, n_samples, n_bins, lohi,
                      target);
   MR_HIP(hipGetLastError());
