@@ -119,7 +119,9 @@ mr_status mr_mlp_fragments(const mr_field_desc* desc, const float* host_mlp, int
  * x, dirs: (n, 3) in world coordinates (mapped into the field's frame when it
  * has a pose); sigma: (n); rgb: (n, 3) or NULL; feat: (n, n_levels*feats)
  * or NULL (interpolated hash features, FP32); raw: (n, density_out) or NULL.
- * Large queries of a 16-level field take about 264 MiB of stream-ordered scratch
+ * Large queries of a 16-level field whose table exceeds 4 MiB (from 196 608
+ * points, with FP16 tables below 2^19 entries from 262 144; none with BF16 MLPs
+ * of one colour layer) take about 264 MiB of stream-ordered scratch
  * (hipMallocFromPoolAsync) from a pool that keeps one such block per device
  * until the last field is destroyed; under capture or without that memory
  * they are evaluated without it, with the same results. */
@@ -146,7 +148,13 @@ mr_status mr_field_build_occupancy(mr_field* f, int32_t res, float thresh, uint8
                                    void* stream);
 
 /* Device pointers of the field's parameters (for training and inspection).
- * table: [L][T][F] in table_dtype; mlp: FP32 flat weights. */
+ * table: [L][T][F] in table_dtype; mlp: FP32 flat weights.
+ * Values written there: every kernel launched afterwards reads the table as it
+ * is.  The MLP weights are read as they are by the occupancy grid, the optical
+ * depth of light samples, and proposal fields (their densities, gradient and
+ * training); renders, queries and proposal targets take the MLPs in the
+ * matrix-core layout that mr_field_create made of the weights it was given
+ * (mr_mlp_fragments), which writes to mlp do not change. */
 mr_status mr_field_params(mr_field* f, void** table, float** mlp, int64_t* n_table,
                           int64_t* n_mlp);
 
@@ -257,7 +265,10 @@ typedef struct {
                                    seconds).  A wave whose wait runs out stops; the rays of
                                    its packets then miss this segment's medium and
                                    mr_render_status reports it.  Never reached in a correct
-                                   run: a bound that keeps every kernel finite */
+                                   run: a bound that keeps every kernel finite.  A value
+                                   above 0 also keeps the camera packets of a small 16-level
+                                   frame on these waves, where 0 lets a block's waves split
+                                   a packet (no waits; the results differ in rounding) */
   int32_t light_depth_samples;  /* with sample_emitters: grid intervals per segment length
                                    for the optical depth along a light sample's shadow
                                    segment (spacing (t_far - t_near) / this), 0..4096;
@@ -282,9 +293,11 @@ typedef struct {
 
 /* Bytes of device workspace for n rays: the ray queues and, for 65 536 rays
  * or more, about 264 MiB (at 256 compute units) in which bounce rays through a
- * 16-level field are marched one hash level at a time.  mr_render also takes
- * a workspace of the queues alone (4096 + 128 n bytes, n rounded up to 64)
- * and then marches them ray by ray: the same results, more slowly. */
+ * 16-level field are marched one hash level at a time.  The size depends on n
+ * alone; a render of another field, or of none, leaves that part untouched.
+ * mr_render, mr_render_graph_create and mr_autotune_search also take a
+ * workspace of the queues alone (4096 + 128 n bytes, n rounded up to 64), and
+ * then these rays are marched ray by ray: the same results, more slowly. */
 size_t mr_render_workspace_size(int64_t n);
 
 /* Render n rays: origins, dirs (n, 3) device, unit directions.
@@ -324,7 +337,10 @@ mr_status mr_render_status(const void* workspace, int64_t* gave_up, void* stream
  *   run; what mr_render_status reports for mr_render).
  * Every call on one device shares that device's array: calls that overlap
  * on one device (two streams, two threads) race and give wrong results;
- * serialise them.  Stage timing (mr_profile_enable) does not cover it. */
+ * serialise them.  Stage timing (mr_profile_enable) does not cover it.
+ * The array holds the queues alone, so bounce rays are marched ray by ray as
+ * with mr_render's smaller workspace: renders of 65 536 rays or more through
+ * a large 16-level field take longer than mr_render's, with the same results. */
 #define MR_NOALLOC_MAX_RAYS 262144
 mr_status mr_render_noalloc(const mr_field* field, const mr_mesh* mesh, int64_t n, const float* origins,
                             const float* dirs, int32_t max_bounces, const int32_t* per_ray_max_bounces,
@@ -451,7 +467,11 @@ typedef struct {
  * on the uniform n_samples grid without surfaces, and split its weights
  * w_i = T_i alpha_i over n_bins (1..64) equal bins of the clipped range by
  * interval overlap.  lohi (n, 2) receives the range ((0, 0) on a miss),
- * targets (n, n_bins) the histograms. */
+ * targets (n, n_bins) the histograms.
+ * Large calls on a 16-level fine field (from 6 144 rays up, by the number of
+ * rays and intervals and the table) take the stream-ordered scratch of
+ * mr_field_query, and go without it, with the same results, under the same
+ * conditions. */
 mr_status mr_proposal_targets(const mr_field* fine, int64_t n, const float* origins, const float* dirs,
                               float t_near, float t_far, int32_t n_samples, int32_t n_bins, float* lohi,
                               float* targets, void* stream);

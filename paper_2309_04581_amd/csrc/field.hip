@@ -41,8 +41,9 @@ uint16_t bf16_rne(float f) {
 // roundings of 2^-24 in sequence; 2e-5 covers both).  A cell whose 8 probes
 // are neither one of them surely >= thresh nor all surely below it is
 // evaluated by probe_sigma, eight lanes per cell.  With the vector-unit MLP on
-// every probe the 128^3 grid of a 16-level field took 8.95 ms; now 2.05, bound
-// by the gathers' lines from beyond L2.
+// every probe the 128^3 grid of a 16-level field took 8.95 ms; now 1.95, bound
+// by the gathers' lines from beyond L2 (113 M of them at 58 G/s, where random
+// single loads reach 59; vector issue 59-68%, matrix cores 15-18% busy).
 constexpr float kOccBand = 2e-5f;
 
 // sigma of one probe on one thread: every hidden sum runs over the features in

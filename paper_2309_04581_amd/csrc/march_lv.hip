@@ -11,8 +11,9 @@ namespace {
 
 // March of bounce rays: the same samples, arithmetic and order as the per-ray
 // march (march_mfma.hip), the same bits.  The bounce segments of the 800x800
-// mid frame (11.7 M samples) went from 7.4 to 5.4 ms in FP32, from 6.9 to 4.7
-// ms with FP16 table and BF16 MLPs.
+// mid frame (11.7 M samples) went from 7.65 to 5.56 ms in FP32, from 6.9 to 4.7
+// ms with FP16 table and BF16 MLPs (default launch shape; with the shape that the
+// search finds for that frame, FP32 6.9 and 5.2).
 template <int NL, int SH, int CL, typename TabT, bool BF>
 __global__ __launch_bounds__(kLvThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_march_lv(
     RayQueue q, const int* __restrict__ count, int* __restrict__ work, FieldView F, const TabT* __restrict__ table,

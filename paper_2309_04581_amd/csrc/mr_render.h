@@ -197,7 +197,24 @@ inline int64_t lv_min_points(const mr_field* f) {
   if (v.mlp_dtype == MR_BF16 && v.c_layers == 1) return INT64_MAX;
   return v.table_dtype == MR_F16 && v.log2_table < 19 ? 262144 : 196608;
 }
-bool lv_field(const mr_field* f);   // a field whose levels fit a die's L2 and whose table does not
+// Fields whose samples are taken one level at a time: 16 levels, a table larger
+// than a die's 4 MiB of L2, and levels of at most 8 MiB.  All levels together /
+// level by level, us, FP32 MLPs unless said, 1 M random points | 64 along each of
+// many rays | 800x800 mid frames:
+//   table   1 MiB, FP32 2^13        303 / 325 | 211 / 293 | 10 124 / 10 808
+//           4 MiB, FP32 2^15        319 / 397 | 209 / 322 | 10 279 / 11 344
+//           8 MiB, FP32 2^16        488 / 415 | 276 / 331 | 11 372 / 11 802
+//           8 MiB, FP16 2^17, BF16  445 / 369 | 255 / 295 |  9 290 /  9 151
+//          16 MiB, FP32 2^17        656 / 422 | 344 / 337 | 12 695 / 11 966
+//   level   4 MiB, FP32 2^19        858 / 494 | 492 / 388 | 15 034 / 12 915
+//           8 MiB, FP32 2^20        913 / 670 | 543 / 500 | 15 655 / 14 139
+//           8 MiB, FP16 2^21, BF16  846 / 596 | 509 / 440 | 14 162 / 12 120
+//          16 MiB, FP32 2^21        941 / 809 | 566 / 571 | 16 009 / 15 142
+//          32 MiB, FP32 2^22        954 / 894 | 574 / 630 | 16 260 / 16 010
+// A level twice the L2 still gains, half of its lines are there; from 16 MiB on
+// points along rays gain nothing.  At 8 MiB of table random points and light
+// samples gain (400x400 emitter frame 7.8 / 7.0 ms) what plain FP32 frames lose.
+bool lv_field(const mr_field* f);
 
 // Scratch for a call without a workspace (false under capture or without
 // memory: the caller then takes the general path), and its return after the
