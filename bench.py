@@ -210,7 +210,7 @@ def proposal_variant(M, sg, sc, F_plain, G, cams, n, plain_img, steps, warmup, t
     march_s = march_ms / steps / 1e3
     flops = 2.0 * (field_macs(sc.field) * fine + PROPOSAL_MACS * prop)
     gbytes = (gather_bytes(sc.field, 2) * fine + 5 * 8 * 2 * 2 * prop) / 1e9
-    roof = {"kernel": "k_march_prop_pk (camera segment) + k_march_prop (later segments)", "bound": "mfma",
+    roof = {"kernel": "k_march_prop_pk (camera segment) + k_march_prop_lv and k_march_prop (later segments)", "bound": "mfma",
             "achieved": round(flops / march_s / 1e12, 2), "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": round(flops / march_s / 1e12 / BF16_MFMA_PEAK_TFLOPS, 4),
             "gather_GB_per_s": round(gbytes / march_s, 1), "peak_hbm": HBM_PEAK_GBS,
@@ -219,7 +219,7 @@ def proposal_variant(M, sg, sc, F_plain, G, cams, n, plain_img, steps, warmup, t
             "stage_ms_per_step": {"closest_hit": round(stage_ms[0] / steps, 3), "march": round(march_ms / steps, 3),
                                   "shade": round(stage_ms[2] / steps, 3)},
             "camera_segment": {"kernel": "k_march_prop_pk", "ms_per_step": round(stage_ms[3] / steps, 3)},
-            "bounce_segments": {"kernel": "k_march_prop", "ms_per_step": round(stage_ms[1] / steps, 3)}}
+            "bounce_segments": {"kernel": "k_march_prop_lv, k_march_prop", "ms_per_step": round(stage_ms[1] / steps, 3)}}
     # the uniform sampler on the same FP16 / BF16 engine: 256 samples (the plain count) and 64
     # (the proposal's budget of 32 + 32)
     uniform = {}
